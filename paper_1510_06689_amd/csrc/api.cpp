@@ -534,6 +534,9 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
             nu_host = nu_read;
             if (!std::isfinite(nu_host))
                 return fail(TK_ERR_NONFINITE, "sthosvd_compress: input holds Inf or NaN");
+            if (flags & 16)
+                return fail(TK_ERR_EIG_NO_CONVERGENCE, "sthosvd_compress: mode %d: the "
+                            "eigensolver's workgroups did not all run", n);
             if (flags & 2)
                 return fail(TK_ERR_CAPACITY, "sthosvd_compress: rank of mode %d exceeds max_ranks",
                             n);
@@ -566,6 +569,9 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
     TK_HIP(hipStreamSynchronize(st));
     if (!std::isfinite(nu_host))
         return fail(TK_ERR_NONFINITE, "sthosvd_compress: input holds Inf or NaN");
+    if (flags & 16)
+        return fail(TK_ERR_EIG_NO_CONVERGENCE, "sthosvd_compress: the eigensolver's workgroups "
+                    "did not all run");
     if (flags & 2) return fail(TK_ERR_CAPACITY, "sthosvd_compress: a rank exceeds max_ranks");
     for (int n = 0; n < N; ++n) {
         out->ranks[n] = cur[n];

@@ -5,13 +5,10 @@
 //   1. Householder reduction to tridiagonal form T = Q^T S Q.  Each step
 //      derives the reflector from the pivot row, forms p = tau A22 v, then
 //      applies the rank-2 update A22 -= v w^T + w v^T.  For J <= 128 the
-//      matrix lives in registers; otherwise it lives in global scratch and
-//      the first J - 128 columns are reduced in panels of eight (the rank-2
-//      updates of a panel are kept as vectors in LDS, applied to the pivot
-//      rows and to A22 x on the fly and to the trailing block once per
-//      panel, as in LAPACK's latrd) before the last 128 x 128 block moves to
-//      registers; reflector k is kept in column k below the diagonal and
-//      copied to global scratch at the end;
+//      matrix lives in one workgroup's registers; otherwise the first
+//      J - 128 columns are reduced by 64 single-wave workgroups that hold it
+//      together (eig_reduce_grid), and one workgroup finishes the last
+//      128 x 128 block; the reflectors go to global scratch;
 //   2. all eigenvalues of T by multisection: groups of threads per
 //      eigenvalue evaluate Sturm counts with the three-term determinant
 //      recurrence of T scaled by a power of two (exact), rescaled by 2^+-300
@@ -39,7 +36,6 @@ namespace tk {
 constexpr int kEigThreads = 1024;
 constexpr int kEigWaves = kEigThreads / 64;
 constexpr int kInvIters = 2;
-constexpr int kPanel = 8;  // columns per panel of the global-memory reduction
 constexpr int kLuArrays = 6;  // u0 (reciprocal), u1, u2, multiplier, pivot flag, x
 constexpr int kMaxVecSlots = TK_MAX_MODE_DIM / 64;  // per-lane elements of one vector
 constexpr int kSweepRows = 4;  // rows per block of the inverse-iteration sweeps
@@ -118,9 +114,12 @@ __device__ __forceinline__ double hash_unit(uint32_t a, uint32_t b) {
     return (double)(z >> 11) * (2.0 / 9007199254740992.0) - 1.0;  // [-1, 1)
 }
 
+// J <= 128: an unused J x J area (its start is the hand-off of a split solve)
+// and the reflectors H (J x J).  J > 128: the exchange slots of the reduction
+// over many waves (products, J x J), H, the exchange slots of the pivot rows
+// (J x J) and the hand-off.
 size_t eig_scratch_doubles(int J) {
-    // A (J*J, used when J > 128) + reflectors H (J*J)
-    return (size_t)2 * J * J + 64;
+    return J > 128 ? (size_t)3 * J * J + (size_t)6 * J + 64 : (size_t)2 * J * J + 64;
 }
 
 // small per-matrix arrays + the [C][rb] partial sums of the tridiagonal step
@@ -382,11 +381,329 @@ __device__ __forceinline__ void tridiag_regs(const double* __restrict__ src, int
     __syncthreads();
 }
 
-// Hand-off area of a split solve (6 J + 4 doubles): the start of the
-// scratch (A's area, J x J, unused or dead once step 1 is done) when it fits,
-// else the 64 spare doubles behind the reflectors (J <= 6).
+// Hand-off area of a split solve (6 J + 4 doubles): for J <= 128 the start of
+// the scratch when it fits there, else the 64 spare doubles behind the
+// reflectors (J <= 6); for J > 128 the end of the scratch.
 __host__ __device__ inline double* eig_handoff(double* scratch, int J) {
+    if (J > 128) return scratch + (size_t)3 * J * J;
     return 6 * J + 4 <= J * J ? scratch : scratch + (size_t)2 * J * J;
+}
+
+// Bounds and scale of T (all threads of the workgroup): red[32..35] receive
+// the widened Gershgorin interval of the scaled T, the scale (a power of two
+// that brings |entries| to at most 1) and the norm bound; ds and e2 the
+// scaled diagonal and squared scaled off-diagonal.  The interval is a
+// minimum and a maximum, so the split over threads changes no bit.
+__device__ __forceinline__ void scale_t(const double* d, const double* e, int J, double* red,
+                                        double* ds, double* e2) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double gl = DBL_MAX, gu = -DBL_MAX;
+    for (int i = tid; i < J; i += kEigThreads) {
+        const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < J ? fabs(e[i]) : 0.0);
+        gl = fmin(gl, d[i] - r);
+        gu = fmax(gu, d[i] + r);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        gl = fmin(gl, __shfl_xor(gl, off, 64));
+        gu = fmax(gu, __shfl_xor(gu, off, 64));
+    }
+    if (lane == 0) {
+        red[wave] = gl;
+        red[kEigWaves + wave] = gu;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < kEigWaves; ++w) {
+            gl = fmin(gl, red[w]);
+            gu = fmax(gu, red[kEigWaves + w]);
+        }
+        const double tnorm = fmax(fabs(gl), fabs(gu));
+        // scale T by a power of two so that |entries| <= 1 (exact)
+        int ex = 0;
+        frexp(tnorm > 0.0 ? tnorm : 1.0, &ex);
+        const double sc = ldexp(1.0, -ex);
+        // widen slightly so that count(gl) = 0 and count(gu) = J hold exactly
+        red[32] = (gl - 2.0 * DBL_EPSILON * tnorm * J) * sc - 0x1p-900;
+        red[33] = (gu + 2.0 * DBL_EPSILON * tnorm * J) * sc + 0x1p-900;
+        red[34] = sc;
+        red[35] = tnorm;
+    }
+    __syncthreads();
+    const double sc = red[34];
+    for (int i = tid; i < J; i += kEigThreads) {
+        ds[i] = d[i] * sc;
+        e2[i] = (e[i] * sc) * (e[i] * sc);
+    }
+    __syncthreads();
+}
+
+// T, beta and the bounds to the hand-off area of a split solve.
+__device__ __forceinline__ void write_handoff(double* ho, int J, const double* d, const double* e,
+                                              const double* beta, const double* ds,
+                                              const double* e2, const double* red) {
+    const int tid = threadIdx.x;
+    for (int i = tid; i < J; i += kEigThreads) {
+        ho[i] = d[i];
+        ho[J + i] = e[i];
+        ho[2 * J + i] = beta[i];
+        ho[3 * J + i] = ds[i];
+        ho[4 * J + i] = e2[i];
+    }
+    if (tid < 4) ho[5 * J + tid] = red[32 + tid];  // gl, gu, sc, tnorm
+}
+
+// ---------------------------------------------- reduction of extents > 128
+//
+// The first J - 128 columns of a matrix too large for one workgroup's
+// registers.  One workgroup streaming A22 from L2 took 12 us per column at
+// J = 256 (one CU's load path and three barriers); here kGridWaves single-wave
+// workgroups hold all of A in registers for the whole reduction (wave w owns
+// rows w + 64 q, lane t of it the columns t + 64 s), so a column costs one
+// exchange between them and no barrier: about 3 us, most of it the trip of a
+// value from one XCD to another.  Whole reductions, this part and the last
+// 128 columns: J = 187 0.80 -> 0.32 ms, J = 250 1.72 -> 0.56, J = 301
+// 3.69 -> 0.78.  All waves on one XCD was slower (J = 301: 0.85 against
+// 0.64 ms for this part).  In column k
+//   - every wave holds the pivot row k and forms the reflector (v, tau) from
+//     it redundantly, with the same bits;
+//   - it publishes p_i = tau (A v)_i for its rows i > k, and the owner of row
+//     k + 1 that row, both as of before this column's update;
+//   - it reads all of p and the row back, forms w = p - (tau / 2)(p.v) v, the
+//     next pivot row, and updates its own rows, A -= v w^T + w v^T.
+// Every (column, entry) has a slot of its own in the scratch, filled with
+// kNotYet beforehand, so a value carries its own arrival: no flags, no order
+// between stores, and 64-bit relaxed agent-scope atomics are all it needs.
+// A result equal to the fill pattern (a NaN payload) is published as the
+// default NaN.  64 waves of one SIMD lane each wait for one another, so all
+// have to be resident: they take at most half a SIMD's registers and no LDS,
+// 2048 of them fit the GPU, and a queue has at most one partly dispatched
+// kernel, which leaves room for 32 queues.  Each wait is bounded all the
+// same: after kGridSpins reads a wave takes NaN for what is missing, waits
+// no more, and sets flag bit 4, which fails the call.
+constexpr int kGridWaves = 64;
+constexpr int kGridTail = 128;  // columns left to the register reduction
+constexpr unsigned long long kNotYet = 0xFFF7A5C39B1E64D2ull;
+constexpr int kGridSpins = 1 << 21;
+
+__device__ __forceinline__ void slot_put(double* p, double v) {
+    unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    if (b == kNotYet) b = 0x7FF8000000000000ull;
+    __hip_atomic_store((unsigned long long*)p, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long slot_get(const double* p) {
+    return __hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ __launch_bounds__(256) void eig_slots_fill(unsigned long long* __restrict__ a,
+                                                      unsigned long long* __restrict__ b,
+                                                      int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) a[i] = b[i] = kNotYet;
+}
+
+// Entry g of a vector spread over the lanes (x[s] of lane t is entry
+// t + 64 s); g is uniform.
+template <int NS>
+__device__ __forceinline__ double grid_entry(const double (&x)[NS], int g) {
+    const int l = g & 63, s = g >> 6;
+    double r = read_lane(x[0], l);
+#pragma unroll
+    for (int q = 1; q < NS; ++q) {
+        const double t = read_lane(x[q], l);
+        r = s == q ? t : r;
+    }
+    return r;
+}
+
+// NS = ceil(J / 64) slots per lane; rows and columns at or past J are zero.
+template <int NS>
+__global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__ S, int J,
+                                                      double* __restrict__ scratch,
+                                                      int* __restrict__ flags) {
+    const int lane = threadIdx.x;
+    const int w = blockIdx.x;
+    double* P = scratch;                        // [J - 128][J] products
+    double* H = scratch + (size_t)J * J;        // reflectors
+    double* Rw = scratch + (size_t)2 * J * J;   // [J - 128][J] pivot rows
+    double* ho = eig_handoff(scratch, J);
+    const int kend = J - kGridTail;
+    double a[NS][NS];  // a[q][s]: row w + 64 q, column lane + 64 s
+    double r[NS];      // pivot row, 0 before column k
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int i = w + 64 * q, j = lane + 64 * s;
+            a[q][s] = (i < J && j < J) ? S[(size_t)i * J + j] : 0.0;
+        }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) r[s] = lane + 64 * s < J ? S[lane + 64 * s] : 0.0;
+    int spins = kGridSpins;
+    if (w == 0 && lane == 0) ho[0] = r[0];  // d_0
+
+    for (int k = 0; k < kend; ++k) {
+        // the owner of row k + 1 publishes it first: it is ready
+        if (w == ((k + 1) & 63)) {
+#pragma unroll
+            for (int q = 0; q < NS; ++q)
+                if (q == ((k + 1) >> 6)) {
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) {
+                        const int j = lane + 64 * s;
+                        if (j > k && j < J) slot_put(Rw + (size_t)k * J + j, a[q][s]);
+                    }
+                }
+        }
+        // reflector of the pivot row's part beyond the diagonal, in the form
+        // of LAPACK's dlarfg (as in the register reduction)
+        const double x0 = grid_entry<NS>(r, k + 1);
+        double sq = 0.0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const double m = lane + 64 * s >= k + 2 ? r[s] : 0.0;
+            sq = fma(m, m, sq);
+        }
+        const double sigma = wave_sum(sq);
+        double tau = 0.0, alpha = x0, inv_v0 = 0.0;
+        if (sigma != 0.0) {
+            const double ss = fma(x0, x0, sigma);
+            const double rs = rsq(ss);
+            const double mu = ss * rs;
+            const double sgn = x0 < 0.0 ? -1.0 : 1.0;
+            alpha = -sgn * mu;
+            tau = fma(fabs(x0), rs, 1.0);
+            inv_v0 = sgn * recip(fabs(x0) + mu);
+        }
+        double v[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int j = lane + 64 * s;
+            v[s] = j >= k + 2 ? r[s] * inv_v0 : (j == k + 1 ? 1.0 : 0.0);
+        }
+        // p of the own rows; lane q ends with row w + 64 q's
+        double mine = 0.0;
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            if (w + 64 * q > k) {  // uniform
+                double t = 0.0;
+#pragma unroll
+                for (int s = 0; s < NS; ++s) t = fma(a[q][s], v[s], t);
+                t = tau * wave_sum(t);
+                mine = lane == q ? t : mine;
+            }
+        }
+        if (lane < NS) {
+            const int i = w + 64 * lane;
+            if (i > k && i < J) slot_put(P + (size_t)k * J + i, mine);
+        }
+        if (w == (k & 63)) {  // one wave, another each column, keeps what is found
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int j = lane + 64 * s;
+                if (j > k && j < J) H[(size_t)k * J + (j - k - 1)] = v[s];
+            }
+            if (lane == 0) {
+                ho[J + k] = alpha;
+                ho[2 * J + k] = tau;
+            }
+        }
+        // everyone's p, and row k + 1
+        double p[NS], rn[NS];
+        for (;;) {
+            bool wait = false;
+            unsigned long long bp[NS], br[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int j = lane + 64 * s;
+                const bool need = j > k && j < J;
+                bp[s] = need ? slot_get(P + (size_t)k * J + j) : 0ull;
+                br[s] = need ? slot_get(Rw + (size_t)k * J + j) : 0ull;
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                wait = wait || bp[s] == kNotYet || br[s] == kNotYet;
+                p[s] = __longlong_as_double((long long)bp[s]);
+                rn[s] = __longlong_as_double((long long)br[s]);
+            }
+            if (!__any(wait)) break;
+            if (--spins <= 0) {  // not reached unless a wave was never run: kNotYet is a NaN
+                spins = 0;
+                if (lane == 0) atomicOr(flags, 16);
+                break;
+            }
+        }
+        double pv = 0.0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) pv = fma(p[s], v[s], pv);
+        const double half = 0.5 * tau * wave_sum(pv);
+        double ww[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) ww[s] = fma(-half, v[s], p[s]);
+        const double w1 = grid_entry<NS>(ww, k + 1);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            // as a row of A is updated, with v_{k+1} = 1
+            const double x = fma(-w1, v[s], rn[s] - ww[s]);
+            r[s] = lane + 64 * s > k ? x : 0.0;
+            if (w == 0 && lane + 64 * s == k + 1) ho[k + 1] = x;  // d_{k+1}
+        }
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            if (w + 64 * q > k) {  // uniform
+                const double vi = read_lane(v[q], w), wi = read_lane(ww[q], w);
+#pragma unroll
+                for (int s = 0; s < NS; ++s) a[q][s] = fma(-wi, v[s], fma(-vi, ww[s], a[q][s]));
+            }
+        }
+    }
+    // the trailing 128 x 128 block, in the room of the reflectors still to come
+    double* T = H + (size_t)kend * J;
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+        const int i = w + 64 * q - kend;
+        if (i >= 0 && i < kGridTail) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int j = lane + 64 * s - kend;
+                if (j >= 0 && j < kGridTail) T[(size_t)i * kGridTail + j] = a[q][s];
+            }
+        }
+    }
+}
+
+// Extents above 128: the register reduction of the trailing block, then the
+// scaling of T; d, e and beta of the first J - 128 columns come from the
+// hand-off, where T goes as for PH = 1 of the solver.
+// LDS: the block's reflectors, five vectors, the reduction's small areas.
+constexpr int kTailRegion = (kGridTail - 2) * kGridTail;
+static size_t eig_tail_lds_bytes(int J) {
+    return ((size_t)kTailRegion + 5 * J + 64 + 8 + 4 * kGridTail) * sizeof(double);
+}
+
+__global__ __launch_bounds__(kEigThreads) void eig_reduce_tail(double* __restrict__ scratch,
+                                                               int J) {
+    extern __shared__ double smem[];
+    double* reg = smem;
+    double* d = smem + kTailRegion;
+    double* e = d + J;
+    double* beta = e + J;
+    double* e2 = beta + J;
+    double* ds = e2 + J;
+    double* red = ds + J;  // 64, then 8, then the vector buffers
+    double* H = scratch + (size_t)J * J;
+    double* ho = eig_handoff(scratch, J);
+    const int kend = J - kGridTail;
+    for (int i = threadIdx.x; i < kend; i += kEigThreads) {
+        d[i] = ho[i];
+        e[i] = ho[J + i];
+        beta[i] = ho[2 * J + i];
+    }
+    tridiag_regs<kGridTail>(H + (size_t)kend * J, kGridTail, kGridTail, kend, J, reg, red, d, e,
+                            beta, H);
+    scale_t(d, e, J, red, ds, e2);
+    write_handoff(ho, J, d, e, beta, ds, e2, red);
 }
 
 // JP = 32, 64, 128: A lives in registers during the tridiagonalisation
@@ -432,236 +749,14 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     }
 
     if constexpr (PH != 3) {
-    if constexpr (JP > 0) {
     // ---- 1. Householder tridiagonalisation, A in registers ---------------
     tridiag_regs<JP>(a.s, J, J, 0, J, reg, red, d, e, beta, H);
-    } else {
-    double* A = a.scratch;  // row-major J x J
-
-    // ---- load S (symmetric) -------------------------------------------
-    for (int idx = tid; idx < J * J; idx += kEigThreads) A[idx] = a.s[idx];
-    __syncthreads();
-
-    // ---- 1. Householder tridiagonalisation ------------------------------
-    // Column-chunked matrix-vector product: thread t owns row i = t % RB of
-    // A22 and the columns j = c, c + C, ... with c = t / RB; the C partials
-    // of each row are added in a fixed order by whoever needs them.
-    int rb = 32;
-    while (rb < J) rb *= 2;
-    const int C = kEigThreads / rb;  // chunks per row
-    const int mi = tid % rb, mc = tid / rb;
-    double* part = red + 64 + 8;  // [C][rb] = kEigThreads partial sums, after misc
-    double* pp = colv;                                    // p
-    double* vv = dots;                                    // v
-    // Once the trailing block is 128 x 128 it moves to registers and the
-    // register path finishes the reduction (when the LDS region can hold
-    // its 126 reflectors at pitch 128).
-    const bool hybrid = J > 128 && region >= 126 * 128;
-    const int kend = hybrid ? J - 128 : J - 2;
-    // Panels of kPanel columns (LAPACK's latrd scheme): inside a panel A keeps
-    // its values from the panel start, and column q of the panel leaves
-    // v_q and w_q = p_q - (kc_q) v_q in LDS (Vs, Ws), so that the matrix the
-    // reduction has reached is A - sum_q (v_q w_q^T + w_q v_q^T).  Row k and
-    // row k + 1 are corrected by those terms, A22 x is formed from the panel
-    // start's A22 and corrected by V (W^T x) + W (V^T x); after the panel the
-    // trailing block takes all of its rank-2 updates in one pass, in a
-    // commutative form so that A stays exactly symmetric.  A22 is read once
-    // per column and written once per panel.
-    double* Vs = reg;              // [kPanel][J], indexed by row of A
-    double* Ws = reg + kPanel * J;
-    double* xs = lam;              // corrected row k (columns k + 1 ..)
-    double* a0s = shift;           // corrected row k + 1 (columns k + 1 ..)
-    for (int k0 = 0; k0 < kend; k0 += kPanel) {
-        const int nq = min(kPanel, kend - k0);
-        for (int c = 0; c < nq; ++c) {
-            const int k = k0 + c, m = J - k - 1;
-            for (int j = tid; j < m; j += kEigThreads) {
-                const int g = k + 1 + j;
-                double xv = A[(size_t)k * J + g], av = A[(size_t)(k + 1) * J + g];
-                for (int q = 0; q < c; ++q) {
-                    const double vg = Vs[q * J + g], wg = Ws[q * J + g];
-                    xv -= Vs[q * J + k] * wg + Ws[q * J + k] * vg;
-                    av -= Vs[q * J + k + 1] * wg + Ws[q * J + k + 1] * vg;
-                }
-                xs[j] = xv;
-                a0s[j] = av;
-            }
-            __syncthreads();
-            // A22 x with the panel start's A22 (read column i so that a
-            // wave's loads are contiguous)
-            {
-                double acc = 0.0;
-                if (mi < m) {
-#pragma unroll 8
-                    for (int j = mc; j < m; j += C)
-                        acc += A[(size_t)(k + 1 + j) * J + (k + 1 + mi)] * xs[j];
-                }
-                part[mc * rb + mi] = acc;
-            }
-            // red[q] = v_q . x, red[c + q] = w_q . x (one wave each)
-            if (wave < 2 * c) {
-                const double* vec = wave < c ? Vs + wave * J : Ws + (wave - c) * J;
-                double sdot = 0.0;
-                for (int j = lane; j < m; j += 64) sdot += vec[k + 1 + j] * xs[j];
-                sdot = wave_sum(sdot);
-                if (lane == 0) red[wave] = sdot;
-            }
-            double sq = 0.0;
-            for (int j = 1 + lane; j < m; j += 64) sq += xs[j] * xs[j];
-            const double sigma = wave_sum(sq);  // same bits in every wave
-            const double x0 = xs[0];
-            double b, mu, v0;
-            if (sigma == 0.0) {
-                b = 0.0;
-                mu = x0;
-                v0 = 1.0;
-            } else {
-                mu = sqrt(x0 * x0 + sigma);
-                v0 = (x0 <= 0.0) ? x0 - mu : -sigma / (x0 + mu);
-                b = 2.0 * v0 * v0 / (sigma + v0 * v0);
-            }
-            const double inv_v0 = 1.0 / v0;
-            if (tid == 0) {
-                double dk = A[(size_t)k * J + k];
-                for (int q = 0; q < c; ++q) {
-                    const double vk = Vs[q * J + k], wk = Ws[q * J + k];
-                    dk -= vk * wk + wk * vk;
-                }
-                d[k] = dk;
-                e[k] = mu;
-                beta[k] = b;
-            }
-            __syncthreads();
-            // v = (x - mu e_1) / v0, so p = b A22 v = b (A22 x - mu A22 e_1) / v0
-            // with A22 e_1 = row k + 1.  Every wave forms kc2 = b p.v from the
-            // partials itself (same order, same bits); wave 0 keeps p, v.
-            double pv = 0.0;
-            for (int j = lane; j < m; j += 64) {
-                double wj = 0.0;
-#pragma unroll 8
-                for (int cc = 0; cc < C; ++cc) wj += part[cc * rb + j];
-                for (int q = 0; q < c; ++q)
-                    wj -= Vs[q * J + k + 1 + j] * red[c + q] + Ws[q * J + k + 1 + j] * red[q];
-                const double pj = b * (wj - mu * a0s[j]) * inv_v0;
-                const double vj = j == 0 ? 1.0 : xs[j] * inv_v0;
-                pv += pj * vj;
-                if (wave == 0) {
-                    pp[j] = pj;
-                    vv[j] = vj;
-                }
-            }
-            const double kc2 = b * wave_sum(pv);  // 2 kc
-            if (wave == 0) {
-                // v p^T + p v^T - 2 kc v v^T = v w^T + w v^T with w = p - kc v;
-                // b = 0 leaves v = w = 0 (no reflection).  Lane j reads the
-                // pp, vv entries it wrote itself.
-                for (int j = lane; j < m; j += 64) {
-                    const double vj = b != 0.0 ? vv[j] : 0.0;
-                    const double wj = b != 0.0 ? pp[j] - 0.5 * kc2 * vv[j] : 0.0;
-                    Vs[c * J + k + 1 + j] = vj;
-                    Ws[c * J + k + 1 + j] = wj;
-                    // the reflector goes below the diagonal of column k
-                    if (b != 0.0) A[(size_t)(k + 1 + j) * J + k] = vj;
-                }
-            }
-            __syncthreads();
-        }
-        // trailing block (rows and columns from k0 + nq) takes the panel's
-        // updates: thread t owns columns t % 256 (+ 256) and rows t / 256 + 4 i
-        const int t0 = k0 + nq, mt = J - t0;
-        const int jc = tid & 255, ir = tid >> 8;
-        for (int jb = jc; jb < mt; jb += 256) {
-            double vj[kPanel], wj[kPanel];
-#pragma unroll
-            for (int q = 0; q < kPanel; ++q) {
-                vj[q] = q < nq ? Vs[q * J + t0 + jb] : 0.0;
-                wj[q] = q < nq ? Ws[q * J + t0 + jb] : 0.0;
-            }
-            // rows in batches of UR whose loads go out together (a row's
-            // store would otherwise hold back the next row's load: the
-            // compiler cannot tell the addresses apart); each element has
-            // one owner, so the values are those of a row-by-row pass
-            constexpr int UR = 4;
-            for (int i0 = ir; i0 < mt; i0 += 4 * UR) {  // uniform over the wave
-                double av[UR];
-#pragma unroll
-                for (int u = 0; u < UR; ++u) {
-                    const int i = min(i0 + 4 * u, mt - 1);  // in bounds; unused past mt
-                    av[u] = A[(size_t)(t0 + i) * J + t0 + jb];
-                }
-#pragma unroll
-                for (int u = 0; u < UR; ++u) {
-                    const int i = i0 + 4 * u;
-                    if (i >= mt) break;  // uniform over the wave
-                    double t = 0.0;
-#pragma unroll
-                    for (int q = 0; q < kPanel; ++q) {
-                        if (q < nq) {
-                            const double vi = Vs[q * J + t0 + i], wi = Ws[q * J + t0 + i];
-                            t = __dadd_rn(t, __dadd_rn(__dmul_rn(vi, wj[q]), __dmul_rn(wi, vj[q])));
-                        }
-                    }
-                    A[(size_t)(t0 + i) * J + t0 + jb] = av[u] - t;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    if (tid == 0 && !hybrid) {
-        if (J >= 2) {
-            d[J - 2] = A[(size_t)(J - 2) * J + (J - 2)];
-            e[J - 2] = A[(size_t)(J - 2) * J + (J - 1)];
-            beta[J - 2] = 0.0;
-        }
-        d[J - 1] = A[(size_t)(J - 1) * J + (J - 1)];
-        e[J - 1] = 0.0;
-        beta[J - 1] = 0.0;
-    }
-    // reflectors to global scratch: the LDS region is reused from step 4 on
-    for (int idx = tid; idx < kend * J; idx += kEigThreads) {
-        const int k = idx / J, i = idx - k * J;
-        if (i < J - k - 1) H[idx] = A[(size_t)(k + 1 + i) * J + k];
-    }
-    __syncthreads();
-    if (hybrid) tridiag_regs<128>(A + (size_t)kend * J + kend, J, 128, kend, J, reg, red, d, e,
-                                  beta, H);
-    }
-    if (tid == 0) {
-        double gl = DBL_MAX, gu = -DBL_MAX;
-        for (int i = 0; i < J; ++i) {
-            double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i + 1 < J ? fabs(e[i]) : 0.0);
-            gl = fmin(gl, d[i] - r);
-            gu = fmax(gu, d[i] + r);
-        }
-        const double tnorm = fmax(fabs(gl), fabs(gu));
-        // scale T by a power of two so that |entries| <= 1 (exact)
-        int ex = 0;
-        frexp(tnorm > 0.0 ? tnorm : 1.0, &ex);
-        const double sc = ldexp(1.0, -ex);
-        // widen slightly so that count(gl) = 0 and count(gu) = J hold exactly
-        red[32] = (gl - 2.0 * DBL_EPSILON * tnorm * J) * sc - 0x1p-900;
-        red[33] = (gu + 2.0 * DBL_EPSILON * tnorm * J) * sc + 0x1p-900;
-        red[34] = sc;
-        red[35] = tnorm;
-    }
-    __syncthreads();
+    double* ds = dots;  // scaled diagonal
+    scale_t(d, e, J, red, ds, e2);
     sc = red[34];
     tnorm = red[35];
-    double* ds = dots;  // scaled diagonal
-    for (int i = tid; i < J; i += kEigThreads) {
-        ds[i] = d[i] * sc;
-        e2[i] = (e[i] * sc) * (e[i] * sc);
-    }
-    __syncthreads();
     if constexpr (PH == 1) {
-        for (int i = tid; i < J; i += kEigThreads) {
-            ho[i] = d[i];
-            ho[J + i] = e[i];
-            ho[2 * J + i] = beta[i];
-            ho[3 * J + i] = ds[i];
-            ho[4 * J + i] = e2[i];
-        }
-        if (tid < 4) ho[5 * J + tid] = red[32 + tid];  // gl, gu, sc, tnorm
+        write_handoff(ho, J, d, e, beta, ds, e2, red);
         return;
     }
 
@@ -1408,10 +1503,47 @@ static int launch_eig_phase(const EigArgs& a, int region, size_t lds, hipStream_
     return TK_OK;
 }
 
+template <int NS>
+static int launch_reduce_grid(const EigArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(eig_reduce_grid<NS>, dim3(kGridWaves), dim3(64), 0, st, a.s, a.J, a.scratch,
+                       a.flags);
+    TK_HIP(hipGetLastError());
+    return TK_OK;
+}
+
+// Steps 1 of an extent above 128, leaving T in the hand-off area.
+static int launch_reduce_large(const EigArgs& a, hipStream_t st) {
+    const int n = (a.J - kGridTail) * a.J;  // slots of each kind
+    const size_t jj = (size_t)a.J * a.J;
+    hipLaunchKernelGGL(eig_slots_fill, dim3((n + 255) / 256), dim3(256), 0, st,
+                       (unsigned long long*)a.scratch, (unsigned long long*)(a.scratch + 2 * jj),
+                       n);
+    TK_HIP(hipGetLastError());
+    switch ((a.J + 63) / 64) {
+        case 3: TK_TRY(launch_reduce_grid<3>(a, st)); break;
+        case 4: TK_TRY(launch_reduce_grid<4>(a, st)); break;
+        case 5: TK_TRY(launch_reduce_grid<5>(a, st)); break;
+        case 6: TK_TRY(launch_reduce_grid<6>(a, st)); break;
+        case 7: TK_TRY(launch_reduce_grid<7>(a, st)); break;
+        case 8: TK_TRY(launch_reduce_grid<8>(a, st)); break;
+        default: return fail(TK_ERR_UNSUPPORTED, "eigensolver: extent %d", a.J);
+    }
+    const size_t lds = eig_tail_lds_bytes(a.J);
+    TK_HIP(hipFuncSetAttribute((const void*)eig_reduce_tail,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(eig_reduce_tail, dim3(1), dim3(kEigThreads), lds, st, a.scratch, a.J);
+    TK_HIP(hipGetLastError());
+    return TK_OK;
+}
+
 template <int JP>
 static int launch_eig_jp(const EigArgs& a, int region, size_t lds, hipStream_t st) {
-    if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, st);
-    TK_TRY((launch_eig_phase<JP, 1>(a, region, lds, st)));
+    if constexpr (JP > 0) {
+        if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, st);
+        TK_TRY((launch_eig_phase<JP, 1>(a, region, lds, st)));
+    } else {
+        TK_TRY(launch_reduce_large(a, st));
+    }
     hipLaunchKernelGGL(eig_multisect, dim3(a.J), dim3(64), (size_t)2 * a.J * sizeof(double), st,
                        a.scratch, a.J);
     TK_HIP(hipGetLastError());

@@ -190,7 +190,8 @@ struct EigArgs {
     int64_t* rank_out;     // device
     double* disc_out;      // device
     int* flags;            // device status flags (bit 0: no convergence, bit 1: capacity,
-                           // bit 2: rank within the guard margin)
+                           // bit 2: rank within the guard margin, bit 4: the reduction
+                           // of an extent above 128 gave up waiting)
     double* scratch;       // eig_scratch_doubles(J)
     // Guard of a rank found from a split-bf16 Gram.  With Y the unfolding
     // (K columns), Y~ its split representation and D = Y - Y~, the Gram
