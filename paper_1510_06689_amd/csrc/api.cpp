@@ -507,8 +507,6 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
         ea.ncols = (double)v.L * (double)v.B;
         ea.tail_bound = bound_dev + n;
         TK_TRY(launch_eig(ea, st));
-        if (qr) TK_TRY(launch_jw_extract(z_ws, v.J, (int)pl.cap[n], rank_dev + n,
-                                         out->factors_dev[n], st));
 
         int64_t R;
         if (opt->fixed_ranks && s > 0) {
@@ -542,6 +540,9 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
                             n);
             R = rk;
         }
+        TK_TRY(launch_eig_finish(ea, (int)R, st));
+        if (qr) TK_TRY(launch_jw_extract(z_ws, v.J, (int)pl.cap[n], rank_dev + n,
+                                         out->factors_dev[n], st));
         int64_t nxt[TK_MAX_NDIM];
         memcpy(nxt, cur, sizeof cur);
         nxt[n] = R;

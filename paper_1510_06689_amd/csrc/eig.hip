@@ -19,9 +19,12 @@
 //      with partial pivoting kept in LDS, reciprocal pivots, two sweeps),
 //      in batches that fit in LDS, then modified Gram-Schmidt (twice) inside
 //      eigenvalue clusters by one wave;
-//   5. back-transformation X <- Q X, one wave per eigenvector with the
+//   5. back-transformation X <- Q X, 16 lanes per eigenvector with the
 //      vector in registers (no barriers), and a sign rule (largest |entry|
 //      positive, lowest index on ties), written to the factor output.
+// Extents above 128 and ranks of more than one batch run step 4's inverse
+// iteration on a workgroup per batch, and the rest in two more launches once
+// the host knows the rank (launch_eig_finish).
 // Barriers never wait on global stores inside loops: global memory is only
 // written between phases.  One workgroup of 1024 threads, except that from
 // J = 64 on step 2 runs in a launch of its own (eig_multisect, one wave per
@@ -37,7 +40,6 @@ constexpr int kEigThreads = 1024;
 constexpr int kEigWaves = kEigThreads / 64;
 constexpr int kInvIters = 2;
 constexpr int kLuArrays = 6;  // u0 (reciprocal), u1, u2, multiplier, pivot flag, x
-constexpr int kMaxVecSlots = TK_MAX_MODE_DIM / 64;  // per-lane elements of one vector
 constexpr int kSweepRows = 4;  // rows per block of the inverse-iteration sweeps
 
 // Rows of the inverse-iteration arrays: J padded to whole sweep blocks.
@@ -706,6 +708,50 @@ __global__ __launch_bounds__(kEigThreads) void eig_reduce_tail(double* __restric
     write_handoff(ho, J, d, e, beta, ds, e2, red);
 }
 
+// Writes a vector held by 16 lanes (element t = 32 p + 2 l16 + h) to column j
+// of X, its largest |entry| (lowest index on ties) made positive.
+template <int NP>
+__device__ __forceinline__ void signed_store(double* __restrict__ X, int J, int j, bool jok,
+                                             int l16, const double2 (&xr)[NP]) {
+                double bv = -1.0;
+                int bi = J;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const int t = 32 * p + 2 * l16;
+                    if (t < J && fabs(xr[p].x) > bv) {
+                        bv = fabs(xr[p].x);
+                        bi = t;
+                    }
+                    if (t + 1 < J && fabs(xr[p].y) > bv) {
+                        bv = fabs(xr[p].y);
+                        bi = t + 1;
+                    }
+                }
+#pragma unroll
+                for (int off = 8; off > 0; off >>= 1) {  // within the 16-lane group
+                    const double ov = __shfl_xor(bv, off, 64);
+                    const int oi = __shfl_xor(bi, off, 64);
+                    if (ov > bv || (ov == bv && oi < bi)) {
+                        bv = ov;
+                        bi = oi;
+                    }
+                }
+                double at = 0.0;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const int t = 32 * p + 2 * l16;
+                    if (t == bi) at = xr[p].x;
+                    if (t + 1 == bi) at = xr[p].y;
+                }
+                const double sgn = row16_sum(at) < 0.0 ? -1.0 : 1.0;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) {
+                    const int t = 32 * p + 2 * l16;
+                    if (jok && t < J) X[(size_t)j * J + t] = sgn * xr[p].x;
+                    if (jok && t + 1 < J) X[(size_t)j * J + t + 1] = sgn * xr[p].y;
+                }
+}
+
 // JP = 32, 64, 128: A lives in registers during the tridiagonalisation
 // (J <= JP); JP = 0: A lives in the global scratch (J > 128).
 // PH = 0: the whole solver in one launch.  PH = 1: steps 1 and the scaling of
@@ -713,11 +759,17 @@ __global__ __launch_bounds__(kEigThreads) void eig_reduce_tail(double* __restric
 // doubles of the scratch, A's area, unused or free by then) and the launch
 // ends; eig_multisect then finds the eigenvalues with one workgroup each and
 // PH = 3 picks everything up for steps 3 to 5.
-template <int JP, int PH>
+// MULTI (PH = 3): one workgroup per batch of vectors.  Each repeats the rank
+// rule (the first one writes its results) and runs the inverse iteration of
+// its own batch.  With J <= 128 and a rank of one batch the first workgroup
+// goes on to the end; otherwise the vectors of T are left in u for
+// eig_gs_* and eig_back.
+template <int JP, int PH, bool MULTI>
 __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     extern __shared__ double smem[];
     const int J = a.J;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool lead = !MULTI || blockIdx.x == 0;  // uniform: writes the rank rule's results
     double* reg = smem;                        // A (J <= 128) then the LU batch
     double* sv = smem + region;
     double* d = sv;              // J
@@ -819,7 +871,7 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     for (int i = tid; i < Jv; i += kEigThreads) {
         const double v = val(i);
         vals[i] = v;
-        a.lambda[i] = a.aug ? v : lam[i];
+        if (lead) a.lambda[i] = a.aug ? v : lam[i];
     }
     __syncthreads();
 
@@ -872,18 +924,20 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
             if (eps_rule) {
                 const bool below = tau - tail >= bound;
                 const bool above = R == 1 || next - tau >= margin(fmax(next, 0.0), R - 1);
-                if (!(below && above)) a.flags[0] |= 4;
+                if (lead && !(below && above)) a.flags[0] |= 4;
             }
         }
-        if (a.tail_bound) *a.tail_bound = bound;
+        if (lead && a.tail_bound) *a.tail_bound = bound;
         int flag = 0;
         if (R > a.max_rank) {
             flag |= 2;
             R = a.max_rank;
         }
-        *a.rank_out = R;
-        *a.disc_out = fmax(tail, 0.0);
-        if (flag) a.flags[0] |= flag;  // single writer: thread 0 of the only workgroup
+        if (lead) {  // single writer: thread 0 of one workgroup
+            *a.rank_out = R;
+            *a.disc_out = fmax(tail, 0.0);
+            if (flag) a.flags[0] |= flag;
+        }
         misc[0] = R;
         // shifts for inverse iteration: separate (near-)equal eigenvalues
         const double pert = 10.0 * DBL_EPSILON * tnorm;
@@ -926,7 +980,10 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     const int recd = kLuArrays * Jb + 1;  // doubles per record
     const int batch = (int)((size_t)region / ((size_t)recd + 2));
     constexpr int oX = 0, oRP = 1, oU1 = 2, oU2 = 3, oLM = 4, oPV = 5;
-    for (int j0 = 0; j0 < R; j0 += batch) {
+    const int jfirst = MULTI ? (int)blockIdx.x * batch : 0;
+    const int jlast = MULTI ? min(R, jfirst + batch) : R;
+    if (MULTI && jfirst >= R) return;  // uniform over the workgroup
+    for (int j0 = jfirst; j0 < jlast; j0 += batch) {
         const int nb = min(batch, R - j0);
         double* SC1 = reg + (size_t)recd * nb;  // nb: pending scale factors of x
         double* SC2 = SC1 + nb;
@@ -1115,14 +1172,16 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                 (reg[(size_t)jj * recd + kLuArrays * i + oX] * SC1[jj]) * SC2[jj];
         }
     }
+    if constexpr (MULTI)
+        if (JP == 0 || R > batch) return;  // eig_gs_* and eig_back go on
+    if constexpr (JP > 0) {
     __syncthreads();
 
     // Modified Gram-Schmidt, twice, inside clusters (descending order), by
     // wave 0 with the working vector in registers and the others in LDS;
     // cluster starts are found in one pass over the eigenvalues.
     const int nslot = (J + 63) / 64;
-    // per-lane slots of a vector: JP / 64 rounded up on the register path
-    constexpr int kGsSlots = JP > 0 ? (JP + 63) / 64 : kMaxVecSlots;
+    constexpr int kGsSlots = (JP + 63) / 64;  // per-lane slots of a vector
     const double ortol = 1e-3 * tnorm;
     const bool clustered =
         __syncthreads_or(tid >= 1 && tid < R && lam[tid - 1] - lam[tid] <= ortol);
@@ -1184,7 +1243,7 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     // ---- 5. back-transformation X <- Q X, Q = H_0 H_1 ... H_{J-3} -------
     // Sign rule for every vector: the largest |entry| (lowest index on ties)
     // is positive.
-    if constexpr (JP > 0) {
+    {
         // A in registers (J <= JP): the LDS region, free again, takes the
         // reflectors in one coalesced pass at pitch JP with zeros outside
         // k < t < J (Hz[k JP + t] = v_t of reflector k).  Each vector is held
@@ -1244,104 +1303,243 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                     if (k == 1) break;
                 }
             }
-            double bv = -1.0;
-            int bi = J;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int t = 32 * p + 2 * l16;
-                if (t < J && fabs(xr[p].x) > bv) {
-                    bv = fabs(xr[p].x);
-                    bi = t;
-                }
-                if (t + 1 < J && fabs(xr[p].y) > bv) {
-                    bv = fabs(xr[p].y);
-                    bi = t + 1;
-                }
-            }
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) {  // within the 16-lane group
-                const double ov = __shfl_xor(bv, off, 64);
-                const int oi = __shfl_xor(bi, off, 64);
-                if (ov > bv || (ov == bv && oi < bi)) {
-                    bv = ov;
-                    bi = oi;
-                }
-            }
-            double at = 0.0;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int t = 32 * p + 2 * l16;
-                if (t == bi) at = xr[p].x;
-                if (t + 1 == bi) at = xr[p].y;
-            }
-            const double sgn = row16_sum(at) < 0.0 ? -1.0 : 1.0;
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                const int t = 32 * p + 2 * l16;
-                if (jok && t < J) X[(size_t)j * J + t] = sgn * xr[p].x;
-                if (jok && t + 1 < J) X[(size_t)j * J + t + 1] = sgn * xr[p].y;
-            }
-        }
-    } else {
-    // reflectors from global scratch; one wave per vector
-    for (int j = wave; j < R; j += kEigWaves) {
-        double xr[kMaxVecSlots];
-#pragma unroll
-        for (int q = 0; q < kMaxVecSlots; ++q) {
-            const int t = lane + 64 * q;
-            xr[q] = (q < nslot && t < J) ? X[(size_t)j * J + t] : 0.0;
-        }
-        for (int k = J - 3; k >= 0; --k) {
-            const double b = beta[k];
-            if (b == 0.0) continue;  // uniform
-            double hv[kMaxVecSlots];
-            double s = 0.0;
-#pragma unroll
-            for (int q = 0; q < kMaxVecSlots; ++q) {
-                const int t = lane + 64 * q;
-                hv[q] = (q < nslot && t > k && t < J) ? H[(size_t)k * J + (t - k - 1)] : 0.0;
-                s += hv[q] * xr[q];
-            }
-            s = b * wave_sum(s);
-#pragma unroll
-            for (int q = 0; q < kMaxVecSlots; ++q) xr[q] -= s * hv[q];
-        }
-        double bv = -1.0;
-        int bi = J;
-#pragma unroll
-        for (int q = 0; q < kMaxVecSlots; ++q) {
-            const int t = lane + 64 * q;
-            if (q < nslot && t < J && fabs(xr[q]) > bv) {
-                bv = fabs(xr[q]);
-                bi = t;
-            }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double ov = __shfl_xor(bv, off, 64);
-            const int oi = __shfl_xor(bi, off, 64);
-            if (ov > bv || (ov == bv && oi < bi)) {
-                bv = ov;
-                bi = oi;
-            }
-        }
-        double at = 0.0;
-#pragma unroll
-        for (int q = 0; q < kMaxVecSlots; ++q)
-            if (lane + 64 * q == bi) at = xr[q];
-        const double sgn = wave_sum(at) < 0.0 ? -1.0 : 1.0;
-#pragma unroll
-        for (int q = 0; q < kMaxVecSlots; ++q) {
-            const int t = lane + 64 * q;
-            if (q < nslot && t < J) X[(size_t)j * J + t] = sgn * xr[q];
+            signed_store<NP>(X, J, j, jok, l16, xr);
         }
     }
     }
 }
 
+// Steps 4 (second half) and 5 of a solve whose vectors fill more than one
+// workgroup of inverse iteration, in launches of their own.
+//
+// c0[i] of every vector i < R: the first vector of its cluster (eigenvalues
+// no further apart than 1e-3 of T's norm, one to the next).  All threads of
+// the workgroup; R <= TK_MAX_MODE_DIM <= its size.
+__device__ __forceinline__ void cluster_starts(const double* lam, double ortol, int R, int* c0) {
+    const int i = threadIdx.x;
+    int b = 0;
+    if (i < R) {
+        b = i >= 1 && lam[i - 1] - lam[i] <= ortol ? 0 : i;
+        c0[i] = b;
+    }
+    __syncthreads();
+    for (int o = 1; o < R; o *= 2) {  // running maximum
+        const int t = i < R && i >= o ? c0[i - o] : 0;
+        __syncthreads();
+        b = max(b, t);
+        if (i < R) c0[i] = b;
+        __syncthreads();
+    }
+}
+
+// Modified Gram-Schmidt inside the clusters, two sweeps, by one workgroup:
+// vector j, normalised, is taken out of every later vector of its cluster.
+// One workgroup doing all vectors, batch after batch, with a single wave for
+// the Gram-Schmidt, spent 1.79 ms on J = 250, R = 100; spread out, inverse
+// iteration takes 99 us (10 workgroups), this 67 us and eig_back 55 us
+// (J = 128, R = 64: 298 -> 132 us).  Here 16 waves own R / 16 vectors each,
+// in registers, and a step costs one barrier; what bounds it is the wave
+// sums.  NS = ceil(J / 64) slots per lane, at most 16 NV vectors.
+template <int NS, int NV>
+__global__ __launch_bounds__(kEigThreads) void eig_gs_regs(const double* __restrict__ ho,
+                                                           double* __restrict__ X, int J, int R) {
+    __shared__ double xs[2][64 * NS];
+    __shared__ int c0[TK_MAX_MODE_DIM];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    cluster_starts(ho + 5 * J + 4, 1e-3 * ho[5 * J + 3], R, c0);
+    double x[NV][NS];
+#pragma unroll
+    for (int m = 0; m < NV; ++m)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int i = wave + 16 * m, t = lane + 64 * s;
+            x[m][s] = i < R && t < J ? X[(size_t)i * J + t] : 0.0;
+        }
+    int use = 0;  // slots alternate by use, and every use has a barrier
+    for (int sweep = 0; sweep < 2; ++sweep) {
+        static_for<0, NV>([&](auto mc) {
+            constexpr int M = decltype(mc)::value;
+            for (int ow = 0; ow < 16; ++ow) {
+                const int j = 16 * M + ow;
+                if (j >= R) break;  // uniform
+                const int cj = c0[j];
+                const bool next = j + 1 < R && c0[j + 1] <= j;
+                double* slot = xs[use & 1];
+                if (wave == ow) {  // uniform over the wave
+                    if (cj < j) {
+                        double n2 = 0.0;
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) n2 = fma(x[M][s], x[M][s], n2);
+                        n2 = wave_sum(n2);
+                        const double inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) x[M][s] *= inv;
+                    }
+                    if (next) {
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) slot[lane + 64 * s] = x[M][s];
+                    }
+                }
+                if (!next) continue;  // uniform over the workgroup
+                // the slot was last read two uses ago, before the barrier of
+                // the use in between
+                __syncthreads();
+                ++use;
+                double xj[NS];
+#pragma unroll
+                for (int s = 0; s < NS; ++s) xj[s] = slot[lane + 64 * s];
+                double dt[NV];
+#pragma unroll
+                for (int m = M; m < NV; ++m) {
+                    const int i = wave + 16 * m;
+                    dt[m] = 0.0;
+                    if (i > j && i < R && c0[i] <= j) {  // uniform over the wave
+                        double t = 0.0;
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) t = fma(x[m][s], xj[s], t);
+                        dt[m] = wave_sum(t);
+                    }
+                }
+#pragma unroll
+                for (int m = M; m < NV; ++m)
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) x[m][s] = fma(-dt[m], xj[s], x[m][s]);
+            }
+        });
+    }
+#pragma unroll
+    for (int m = 0; m < NV; ++m)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int i = wave + 16 * m, t = lane + 64 * s;
+            if (i < R && t < J) X[(size_t)i * J + t] = x[m][s];
+        }
+}
+
+// The same with the vectors in global memory, for ranks whose vectors do not
+// fit one workgroup's registers.  A wave rewrites only its own vectors, and
+// vector j is read by all between two barriers.
+__global__ __launch_bounds__(kEigThreads) void eig_gs_mem(const double* __restrict__ ho,
+                                                          double* X, int J, int R) {
+    __shared__ double xs[2][TK_MAX_MODE_DIM];
+    __shared__ int c0[TK_MAX_MODE_DIM];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    cluster_starts(ho + 5 * J + 4, 1e-3 * ho[5 * J + 3], R, c0);
+    int use = 0;
+    for (int sweep = 0; sweep < 2; ++sweep)
+        for (int j = 0; j < R; ++j) {
+            const bool next = j + 1 < R && c0[j + 1] <= j;
+            double* slot = xs[use & 1];
+            if (wave == (j & 15)) {
+                double* xv = X + (size_t)j * J;
+                double inv = 1.0;
+                if (c0[j] < j) {
+                    double n2 = 0.0;
+                    for (int t = lane; t < J; t += 64) n2 = fma(xv[t], xv[t], n2);
+                    n2 = wave_sum(n2);
+                    inv = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+                }
+                for (int t = lane; t < J; t += 64) {
+                    const double v = xv[t] * inv;
+                    xv[t] = v;
+                    if (next) slot[t] = v;
+                }
+            }
+            if (!next) continue;  // uniform over the workgroup
+            __syncthreads();
+            ++use;
+            for (int i = wave + 16 * ((j + 16 - wave) / 16); i < R && c0[i] <= j; i += 16) {
+                double* xi = X + (size_t)i * J;
+                double t0 = 0.0;
+                for (int t = lane; t < J; t += 64) t0 = fma(xi[t], slot[t], t0);
+                t0 = wave_sum(t0);
+                for (int t = lane; t < J; t += 64) xi[t] = fma(-t0, slot[t], xi[t]);
+            }
+        }
+}
+
+// Back-transformation and sign rule, 16 vectors per workgroup of 4 waves,
+// each vector held by 16 lanes as in the one-workgroup solver: element
+// t = 32 p + 2 l + h at lane l.  The reflectors pass through LDS in chunks of
+// eight, the next chunk's loads in flight while one is applied.  (Reading each
+// reflector from L2 when it was due cost about 0.6 us per reflector.)
+constexpr int kBackThreads = 256;
+constexpr int kBackChunk = 8;
+
+template <int NP>
+__global__ __launch_bounds__(kBackThreads) void eig_back(const double* __restrict__ scratch,
+                                                         double* __restrict__ X, int J, int R) {
+    constexpr int W = 32 * NP;  // padded vector length
+    constexpr int NL = kBackChunk * W / kBackThreads;
+    extern __shared__ double hs[];  // [2][kBackChunk][W], then [2][kBackChunk] betas
+    double* sb = hs + 2 * kBackChunk * W;
+    const double* H = scratch + (size_t)J * J;
+    const double* beta = eig_handoff(const_cast<double*>(scratch), J) + 2 * J;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int g = lane >> 4, l16 = lane & 15;
+    const int j = 16 * (int)blockIdx.x + 4 * wave + g;
+    const bool jok = j < R;
+    double2 xr[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int t = 32 * p + 2 * l16;
+        xr[p].x = (jok && t < J) ? X[(size_t)j * J + t] : 0.0;
+        xr[p].y = (jok && t + 1 < J) ? X[(size_t)j * J + t + 1] : 0.0;
+    }
+    double hv[NL], bv = 0.0;
+    auto load = [&](int c) {  // chunk c: reflectors J - 3 - 8 c downward
+        const int k0 = J - 3 - kBackChunk * c;
+#pragma unroll
+        for (int n = 0; n < NL; ++n) {
+            const int idx = tid + kBackThreads * n;
+            const int k = k0 - idx / W, t = idx % W;
+            hv[n] = (k >= 0 && t > k && t < J) ? H[(size_t)k * J + (t - k - 1)] : 0.0;
+        }
+        if (tid < kBackChunk) bv = k0 - tid >= 0 ? beta[k0 - tid] : 0.0;
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int n = 0; n < NL; ++n) hs[b * kBackChunk * W + tid + kBackThreads * n] = hv[n];
+        if (tid < kBackChunk) sb[b * kBackChunk + tid] = bv;
+    };
+    const int nc = (J - 2 + kBackChunk - 1) / kBackChunk;
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int c = 0; c < nc; ++c) {
+        if (c + 1 < nc) load(c + 1);
+        const double* hb = hs + (c & 1) * kBackChunk * W;
+#pragma unroll
+        for (int u = 0; u < kBackChunk; ++u) {
+            const double b = sb[(c & 1) * kBackChunk + u];
+            const double2* hk = reinterpret_cast<const double2*>(hb + u * W);
+            double2 h[NP];
+#pragma unroll
+            for (int p = 0; p < NP; ++p) h[p] = hk[16 * p + l16];
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                s0 = fma(h[p].x, xr[p].x, s0);
+                s1 = fma(h[p].y, xr[p].y, s1);
+            }
+            const double sk = b * row16_sum(s0 + s1);
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                xr[p].x = fma(-sk, h[p].x, xr[p].x);
+                xr[p].y = fma(-sk, h[p].y, xr[p].y);
+            }
+        }
+        if (c + 1 < nc) store((c + 1) & 1);
+        __syncthreads();
+    }
+    signed_store<NP>(X, J, j, jok, l16, xr);
+}
+
 template <int JP, int PH>
 __global__ __launch_bounds__(kEigThreads) void eig_kernel(EigArgs a, int region) {
-    eig_body<JP, PH>(a, region);
+    eig_body<JP, PH, PH == 3>(a, region);
 }
 
 // Step 2 of a split solve by multisection on the scaled T in the hand-off
@@ -1434,7 +1632,7 @@ __global__ __launch_bounds__(kEigThreads) void eig_batched(const EigArgs* __rest
         a.guard = 0.0;  // an FP64 Gram: plain rank rule
         a.split_stats = nullptr;
     }
-    eig_body<JP, PH>(a, region);
+    eig_body<JP, PH, false>(a, region);
     if (PH != 1 && (conditional || (f0 & 8))) {  // the pass's last launch
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -1493,12 +1691,18 @@ int launch_eig_batched(const EigArgs* args_dev, int count, int jmax, int conditi
 // over J workgroups, vectors): the multisection then runs on the whole GPU.
 constexpr int kSplitEig = 64;
 
+// Vectors of inverse iteration that one workgroup's LDS region holds.
+static int eig_batch(int J) {
+    const size_t region = eig_region_doubles_jp(J, eig_jp(J));
+    return (int)(region / ((size_t)kLuArrays * eig_sweep_rows(J) + 3));
+}
+
 template <int JP, int PH>
-static int launch_eig_phase(const EigArgs& a, int region, size_t lds, hipStream_t st) {
+static int launch_eig_phase(const EigArgs& a, int region, size_t lds, int wgs, hipStream_t st) {
     auto fn = eig_kernel<JP, PH>;
     TK_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)lds));
-    hipLaunchKernelGGL(fn, dim3(1), dim3(kEigThreads), lds, st, a, region);
+    hipLaunchKernelGGL(fn, dim3(wgs), dim3(kEigThreads), lds, st, a, region);
     TK_HIP(hipGetLastError());
     return TK_OK;
 }
@@ -1539,15 +1743,20 @@ static int launch_reduce_large(const EigArgs& a, hipStream_t st) {
 template <int JP>
 static int launch_eig_jp(const EigArgs& a, int region, size_t lds, hipStream_t st) {
     if constexpr (JP > 0) {
-        if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, st);
-        TK_TRY((launch_eig_phase<JP, 1>(a, region, lds, st)));
+        if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, 1, st);
+        TK_TRY((launch_eig_phase<JP, 1>(a, region, lds, 1, st)));
     } else {
         TK_TRY(launch_reduce_large(a, st));
     }
     hipLaunchKernelGGL(eig_multisect, dim3(a.J), dim3(64), (size_t)2 * a.J * sizeof(double), st,
                        a.scratch, a.J);
     TK_HIP(hipGetLastError());
-    return launch_eig_phase<JP, 3>(a, region, lds, st);
+    // a workgroup per batch of vectors up to the largest rank there can be
+    const int jv = a.aug ? a.J / 2 : a.J;
+    int cap = a.fixed_rank > 0 && a.fixed_rank < jv ? a.fixed_rank : jv;
+    if (a.max_rank < cap) cap = a.max_rank;
+    const int nb = eig_batch(a.J);
+    return launch_eig_phase<JP, 3>(a, region, lds, (cap + nb - 1) / nb, st);
 }
 
 int launch_eig(const EigArgs& a, hipStream_t st) {
@@ -1561,6 +1770,51 @@ int launch_eig(const EigArgs& a, hipStream_t st) {
         case 128: return launch_eig_jp<128>(a, region, lds, st);
         default: return launch_eig_jp<0>(a, region, lds, st);
     }
+}
+
+template <int NS, int NV>
+static int launch_gs_t(const EigArgs& a, int R, hipStream_t st) {
+    const double* ho = eig_handoff(a.scratch, a.J);
+    if (R <= 16 * NV)
+        hipLaunchKernelGGL((eig_gs_regs<NS, NV>), dim3(1), dim3(kEigThreads), 0, st, ho, a.u, a.J,
+                           R);
+    else
+        hipLaunchKernelGGL(eig_gs_mem, dim3(1), dim3(kEigThreads), 0, st, ho, a.u, a.J, R);
+    TK_HIP(hipGetLastError());
+    return TK_OK;
+}
+
+template <int NP>
+static int launch_back_t(const EigArgs& a, int R, hipStream_t st) {
+    const size_t lds = (size_t)2 * kBackChunk * (32 * NP + 1) * sizeof(double);
+    auto fn = eig_back<NP>;
+    TK_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds));
+    hipLaunchKernelGGL(fn, dim3((R + 15) / 16), dim3(kBackThreads), lds, st, a.scratch, a.u, a.J,
+                       R);
+    TK_HIP(hipGetLastError());
+    return TK_OK;
+}
+
+int launch_eig_finish(const EigArgs& a, int R, hipStream_t st) {
+    // the solver itself ends what one launch (J < 64) or one batch holds
+    if (a.J < kSplitEig || (a.J <= 128 && R <= eig_batch(a.J))) return TK_OK;
+    // vectors per wave of the register version: at most 40 doubles per lane
+    switch ((a.J + 63) / 64) {
+        case 1: TK_TRY((launch_gs_t<1, 4>(a, R, st))); break;
+        case 2: TK_TRY((launch_gs_t<2, 8>(a, R, st))); break;
+        case 3: TK_TRY((launch_gs_t<3, 12>(a, R, st))); break;
+        case 4: TK_TRY((launch_gs_t<4, 10>(a, R, st))); break;
+        case 5: TK_TRY((launch_gs_t<5, 8>(a, R, st))); break;
+        case 6: TK_TRY((launch_gs_t<6, 6>(a, R, st))); break;
+        case 7: TK_TRY((launch_gs_t<7, 5>(a, R, st))); break;
+        default: TK_TRY((launch_gs_t<8, 5>(a, R, st))); break;
+    }
+    if (a.J <= 128) return launch_back_t<4>(a, R, st);
+    if (a.J <= 192) return launch_back_t<6>(a, R, st);
+    if (a.J <= 256) return launch_back_t<8>(a, R, st);
+    if (a.J <= 384) return launch_back_t<12>(a, R, st);
+    return launch_back_t<16>(a, R, st);
 }
 
 }  // namespace tk

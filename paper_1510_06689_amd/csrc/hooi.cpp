@@ -194,6 +194,7 @@ int tucker_hooi(const tk_shape* x, const void* x_dev, const tk_options* opt, int
             ea.scratch = eig_ws;
             ea.guard = 0.0;
             TK_TRY(launch_eig(ea, st));
+            TK_TRY(launch_eig_finish(ea, (int)R[n], st));
         }
         // core from the last mode's Y (every mode but N already applied)
         {

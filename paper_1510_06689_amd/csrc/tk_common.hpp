@@ -271,6 +271,10 @@ inline bool mixed_takes_fp64_gram(const ModeView& v) {
 }
 size_t eig_scratch_doubles(int J);
 int launch_eig(const EigArgs& a, hipStream_t st);
+// Completes the vectors of a launch_eig once its rank R is known on the host
+// (Gram-Schmidt and back-transformation over several workgroups); nothing to
+// do where launch_eig ended them itself.  Must follow it on the same stream.
+int launch_eig_finish(const EigArgs& a, int R, hipStream_t st);
 size_t eig_lds_bytes(int J);
 int launch_eig_batched(const EigArgs* args_dev, int count, int jmax, int conditional,
                        int mode_bit, hipStream_t st);

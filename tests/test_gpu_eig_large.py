@@ -52,3 +52,20 @@ def test_nonfinite_input_ends():
     with pytest.raises(tucker.TuckerError) as err:
         tucker.sthosvd(d, 1e-4)
     assert "NONFINITE" in str(err.value)
+
+
+@pytest.mark.parametrize("j,r,steps", [
+    (64, 43, 1), (64, 64, 1), (97, 29, 1), (128, 22, 1), (128, 128, 1),     # just past one workgroup's batch, and all
+    (129, 17, 1), (193, 160, 1), (250, 100, 1), (257, 129, 1), (385, 96, 1),  # registers, their limits and past them
+    (150, 40, 5), (300, 33, 11),                                            # clusters with gaps in between
+])
+def test_many_vectors(j, r, steps):
+    """Ranks beyond one workgroup of inverse iteration: Gram-Schmidt inside
+    clusters (eigenvalues in groups of `steps`, 1e-4 apart inside one and
+    clearly apart from the next; with steps = 1 one slow decay) and the
+    back-transformation over several workgroups."""
+    rng = np.random.default_rng(1000 * j + r)
+    q, _ = np.linalg.qr(rng.standard_normal((j, j)))
+    k = np.arange(j)
+    lam = 0.995 ** k if steps == 1 else 0.9 ** (k // steps) * (1 + 1e-4 * (steps - k % steps))
+    _check(q * np.sqrt(lam), r)
