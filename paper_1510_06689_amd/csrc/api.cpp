@@ -2,6 +2,7 @@
 // planning, and the mode loop of Alg. 1 (ST-HOSVD) and of the Tucker
 // reconstruction (Sec. II-C).
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstring>
@@ -66,39 +67,92 @@ static bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
 
 using namespace tk;
 
-// Scalar block of one compression (device): [0] ||X||^2, [1..8] discarded
-// sums, [16..23] ranks, [32] status flags, [40..41] split statistics of the
-// last split-bf16 Gram, [48..55] tail-sum error bounds.  The per-mode readback copies
-// its first 33 doubles in one transfer into pinned host memory allocated
-// once per thread (kept for the thread's lifetime: 512 bytes); pageable
-// stack memory is the fallback if that allocation fails.
-static double* pinned_scalars() {
-    static thread_local double* p = nullptr;
+// Pinned host memory of a calling thread, allocated once and kept for the
+// thread's lifetime (512 bytes): kHostScalars doubles and the sequence number
+// that the eigensolver writes behind them (EigArgs::host).  A call is
+// synchronous, so a thread has one publication under way at most; one that a
+// failed call did not see arrive is waited for before the block is used again.
+struct HostBlock {
+    double* p = nullptr;    // as the host sees it
+    double* dev = nullptr;  // as the device sees it
+    uint64_t seq = 0;
+    bool pending = false;
+};
+
+static HostBlock* host_block() {  // NULL: pinned memory could not be had
+    static thread_local HostBlock b;
     static thread_local bool tried = false;
     if (!tried) {
         tried = true;
-        if (hipHostMalloc((void**)&p, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-            p = nullptr;
+        if (hipHostMalloc((void**)&b.p, 64 * sizeof(double),
+                          hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) !=
+            hipSuccess) {
+            b.p = nullptr;
             (void)hipGetLastError();
+        } else {
+            memset(b.p, 0, 64 * sizeof(double));
+            if (hipHostGetDevicePointer((void**)&b.dev, b.p, 0) != hipSuccess) {
+                b.dev = nullptr;
+                (void)hipGetLastError();
+            }
         }
     }
-    return p;
+    return b.p ? &b : nullptr;
 }
 
-static int read_scalars(const double* scal_dev, hipStream_t st, int n, int64_t* rank, double* nu,
-                        int* flags) {
-    double local[33];
-    double* h = pinned_scalars();
-    if (!h) h = local;
-    TK_HIP(hipMemcpyAsync(h, scal_dev, 33 * sizeof(double), hipMemcpyDeviceToHost, st));
+int tk::read_block(const double* dev, size_t n, double* host, hipStream_t st) {
+    HostBlock* hb = host_block();
+    if (hb && hb->pending) {
+        TK_HIP(hipDeviceSynchronize());
+        hb->pending = false;
+    }
+    double* h = hb ? hb->p : host;  // pageable memory is the fallback
+    TK_HIP(hipMemcpyAsync(h, dev, n * sizeof(double), hipMemcpyDeviceToHost, st));
     TK_HIP(hipStreamSynchronize(st));
-    int64_t r;
-    int f;
-    memcpy(&r, h + 16 + n, sizeof r);
-    memcpy(&f, h + 32, sizeof f);
-    *rank = r;
-    *nu = h[0];
-    *flags = f;
+    if (h != host) memcpy(host, h, n * sizeof(double));
+    return TK_OK;
+}
+
+// Makes the eigensolver launched with ea publish the scalar block.
+static int publish_arm(HostBlock* hb, const double* scal, EigArgs* ea) {
+    ea->host = nullptr;
+    if (!hb || !hb->dev) return TK_OK;
+    if (hb->pending) TK_HIP(hipDeviceSynchronize());
+    ea->host = hb->dev;
+    ea->host_scal = scal;
+    ea->host_seq = ++hb->seq;
+    hb->pending = true;
+    return TK_OK;
+}
+
+static bool published(const HostBlock* hb, uint64_t seq) {
+    return __atomic_load_n((const uint64_t*)(hb->p + kHostScalars), __ATOMIC_ACQUIRE) == seq;
+}
+
+// The scalar block once the eigensolver launched with ea has decided the
+// rank; its vectors, and what the host enqueues next, are still to run.  (A
+// copy and a synchronisation instead cost 30 to 40 us of idle device per
+// mode: the copy's launch, the host's wake-up and the next launch's way.)
+// The stream is looked at every 2 ms, so that a failed one ends the wait.
+static int wait_scalars(HostBlock* hb, const EigArgs& ea, const double* scal, double* out,
+                        hipStream_t st) {
+    if (!ea.host) return read_block(scal, kHostScalars, out, st);
+    auto look = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    while (!published(hb, ea.host_seq)) {
+        for (int i = 0; i < 64; ++i) __builtin_ia32_pause();
+        if (std::chrono::steady_clock::now() < look) continue;
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+        } else if (e != hipSuccess) {
+            return fail(TK_ERR_HIP, "waiting for a rank: %s", hipGetErrorString(e));
+        } else if (!published(hb, ea.host_seq)) {
+            return read_block(scal, kHostScalars, out, st);  // done without it
+        }
+        look = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    }
+    hb->pending = false;
+    memcpy(out, hb->p, kHostScalars * sizeof(double));
     return TK_OK;
 }
 
@@ -462,7 +516,14 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
     uint32_t fp64_modes = 0;
     const int ttm_prec = opt->fixed_ranks ? opt->ttm_precision
                                           : ttm_precision_for_eps(opt->ttm_precision, eps2n);
-    double nu_host = 0.0;
+    HostBlock* hb = host_block();
+    EigArgs final_ea;
+    double sc[kHostScalars];
+    auto flags_of = [](const double* block) {
+        int f;
+        memcpy(&f, block + 32, sizeof f);
+        return f;
+    };
 
     for (int s = 0; s < N; ++s) {
         const int n = pl.order[s];
@@ -506,18 +567,19 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
         ea.split_stats = mixed ? stats_dev : nullptr;
         ea.ncols = (double)v.L * (double)v.B;
         ea.tail_bound = bound_dev + n;
+        // the rank (and, after the first Gram, ||X||^2) must reach the host;
+        // with fixed ranks only the last mode's scalars do, after the call
+        const bool known = opt->fixed_ranks && s > 0;
+        if (!known || s + 1 == N) TK_TRY(publish_arm(hb, scal, &ea));
+        if (s + 1 == N) final_ea = ea;
         TK_TRY(launch_eig(ea, st));
 
         int64_t R;
-        if (opt->fixed_ranks && s > 0) {
+        if (known) {
             R = opt->fixed_ranks[n];
         } else {
-            // the rank (and, after the first Gram, ||X||^2) must reach the host:
-            // one copy of the scalar block into pinned memory, then a sync
-            int64_t rk;
-            int flags;
-            double nu_read;
-            TK_TRY(read_scalars(scal, st, n, &rk, &nu_read, &flags));
+            TK_TRY(wait_scalars(hb, ea, scal, sc, st));
+            int flags = flags_of(sc);
             if (flags & 4) {
                 // the mixed Gram cannot certify this rank: redo the mode in FP64
                 TK_HIP(hipMemsetAsync(flags_dev, 0, sizeof(int), st));
@@ -525,12 +587,16 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
                                    gram_ws, pl.gram_bytes, st));
                 ea.guard = 0.0;  // an FP64 Gram: plain rank rule
                 ea.split_stats = nullptr;
+                TK_TRY(publish_arm(hb, scal, &ea));
+                if (s + 1 == N) final_ea = ea;
                 TK_TRY(launch_eig(ea, st));
-                TK_TRY(read_scalars(scal, st, n, &rk, &nu_read, &flags));
+                TK_TRY(wait_scalars(hb, ea, scal, sc, st));
+                flags = flags_of(sc);
                 fp64_modes |= 1u << n;
             }
-            nu_host = nu_read;
-            if (!std::isfinite(nu_host))
+            const bool finite = std::isfinite(sc[0]);
+            if (!finite || (flags & (2 | 16))) TK_HIP(hipStreamSynchronize(st));
+            if (!finite)
                 return fail(TK_ERR_NONFINITE, "sthosvd_compress: input holds Inf or NaN");
             if (flags & 16)
                 return fail(TK_ERR_EIG_NO_CONVERGENCE, "sthosvd_compress: mode %d: the "
@@ -538,7 +604,7 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
             if (flags & 2)
                 return fail(TK_ERR_CAPACITY, "sthosvd_compress: rank of mode %d exceeds max_ranks",
                             n);
-            R = rk;
+            memcpy(&R, sc + 16 + n, sizeof R);
         }
         TK_TRY(launch_eig_finish(ea, (int)R, st));
         if (qr) TK_TRY(launch_jw_extract(z_ws, v.J, (int)pl.cap[n], rank_dev + n,
@@ -550,9 +616,11 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
         if (s + 1 == N) {
             int64_t ncore = 1;
             for (int k = 0; k < N; ++k) ncore *= nxt[k];
-            if (ncore > out->core_capacity)
+            if (ncore > out->core_capacity) {
+                TK_HIP(hipStreamSynchronize(st));
                 return fail(TK_ERR_CAPACITY, "sthosvd_compress: core has %lld elements, capacity "
                             "%lld", (long long)ncore, (long long)out->core_capacity);
+            }
             dst = out->core_dev;
         } else {
             dst = ybuf[s & 1];
@@ -561,13 +629,16 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
         memcpy(cur, nxt, sizeof cur);
         ycur = dst;
     }
-    double disc[TK_MAX_NDIM], bounds[TK_MAX_NDIM];
-    int flags = 0;
-    TK_HIP(hipMemcpyAsync(disc, disc_dev, N * sizeof(double), hipMemcpyDeviceToHost, st));
-    TK_HIP(hipMemcpyAsync(bounds, bound_dev, N * sizeof(double), hipMemcpyDeviceToHost, st));
-    TK_HIP(hipMemcpyAsync(&nu_host, nu_dev, sizeof(double), hipMemcpyDeviceToHost, st));
-    TK_HIP(hipMemcpyAsync(&flags, flags_dev, sizeof(int), hipMemcpyDeviceToHost, st));
+    // the last mode's publication holds every mode's scalars
     TK_HIP(hipStreamSynchronize(st));
+    if (final_ea.host && published(hb, final_ea.host_seq)) {
+        hb->pending = false;
+        memcpy(sc, hb->p, sizeof sc);
+    } else {
+        TK_TRY(read_block(scal, kHostScalars, sc, st));
+    }
+    const double nu_host = sc[0];
+    const int flags = flags_of(sc);
     if (!std::isfinite(nu_host))
         return fail(TK_ERR_NONFINITE, "sthosvd_compress: input holds Inf or NaN");
     if (flags & 16)
@@ -576,8 +647,8 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
     if (flags & 2) return fail(TK_ERR_CAPACITY, "sthosvd_compress: a rank exceeds max_ranks");
     for (int n = 0; n < N; ++n) {
         out->ranks[n] = cur[n];
-        out->discarded[n] = disc[n];
-        out->tail_error_bound[n] = bounds[n];
+        out->discarded[n] = sc[1 + n];
+        out->tail_error_bound[n] = sc[48 + n];
     }
     out->norm2 = nu_host;
     out->fp64_modes = fp64_modes;
@@ -710,9 +781,7 @@ int tucker_error_metrics(const tk_shape* x, const void* x_dev, const void* xhat_
     double* part = (double*)c.take((size_t)3 * nb * sizeof(double));
     double* out3 = (double*)c.take(3 * sizeof(double));
     TK_TRY(launch_error_metrics(x_dev, xhat_dev, x->dtype, n, part, nb, out3, st));
-    TK_HIP(hipMemcpyAsync(out_host, out3, 3 * sizeof(double), hipMemcpyDeviceToHost, st));
-    TK_HIP(hipStreamSynchronize(st));
-    return TK_OK;
+    return read_block(out3, 3, out_host, st);
 }
 
 int sthosvd_mode_order(int ndim, const int64_t* dims, const int64_t* ranks, int rule,

@@ -995,6 +995,17 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                 i < J ? hash_unit((uint32_t)(j0 + jj), (uint32_t)i) : 0.0;
         }
         __syncthreads();
+        // meanwhile the last wave hands the call's scalars to the host, which
+        // waits for the rank: it can enqueue what follows while this runs
+        if (lead && a.host != nullptr && j0 == jfirst && wave == kEigWaves - 1) {
+            if (lane < kHostScalars)
+                __hip_atomic_store(a.host + lane, a.host_scal[lane], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
+            __threadfence_system();
+            if (lane == 0)
+                __hip_atomic_store((uint64_t*)(a.host + kHostScalars), a.host_seq,
+                                   __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
         if (tid < nb) {
             constexpr int IB = kSweepRows;
             constexpr int W = kLuArrays;

@@ -85,12 +85,6 @@ HooiPlan plan_hooi(const tk_shape* x, const tk_options* opt) {
     return pl;
 }
 
-int read_back(const double* dev, size_t n, double* host, hipStream_t st) {
-    TK_HIP(hipMemcpyAsync(host, dev, n * sizeof(double), hipMemcpyDeviceToHost, st));
-    TK_HIP(hipStreamSynchronize(st));
-    return TK_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -151,7 +145,7 @@ int tucker_hooi(const tk_shape* x, const void* x_dev, const tk_options* opt, int
         const ModeView v = mode_view(R, N, 0);
         TK_TRY(launch_gram(out->core_dev, x->dtype, v, TK_GRAM_FP64, S, g2_dev, gram_ws,
                            pl.gram_bytes, st));
-        return read_back(g2_dev, 1, g2, st);
+        return read_block(g2_dev, 1, g2, st);
     };
     const double nu = out->norm2;
     double g2 = 0.0;
@@ -217,7 +211,7 @@ int tucker_hooi(const tk_shape* x, const void* x_dev, const tk_options* opt, int
     }
     if (done > 0) {
         double sc[33];
-        TK_TRY(read_back(scal, 33, sc, st));
+        TK_TRY(read_block(scal, 33, sc, st));
         int flags;
         memcpy(&flags, sc + 32, sizeof flags);
         if (flags & 16)

@@ -174,6 +174,14 @@ int launch_gram(const void* y, int dtype, const ModeView& v, int precision, doub
 int launch_ttm(const void* y, int dtype, const ModeView& v, const double* m, int64_t K,
                int64_t ldm, int transpose, int precision, void* z, hipStream_t st);
 
+// Scalar block of one compression (device): [0] ||X||^2, [1..8] discarded
+// sums, [16..23] ranks, [32] status flags, [40..41] split statistics of the
+// last split-bf16 Gram, [48..55] tail-sum error bounds.
+constexpr int kHostScalars = 56;
+// n <= kHostScalars doubles from the device through the calling thread's
+// pinned block; synchronises the stream.
+int read_block(const double* dev, size_t n, double* host, hipStream_t st);
+
 // Eigendecomposition + truncation of one J x J FP64 Gram matrix (Alg. 1).
 // rank_mode: 0 = eps rule with tau = eps2_over_n * (*nu), 1 = fixed rank.
 // Writes lambda (J, descending), U (J x R column-major, ld J) into u_out,
@@ -215,6 +223,12 @@ struct EigArgs {
     double ncols = 0.0;                   // K, the unfolding's columns (an upper bound)
     double* tail_bound = nullptr;         // device out (may be NULL): the bound on
                                           // |t_R - t~_R|; 0 without the guard
+    // Publication to the host: once the rank is decided the kernel copies the
+    // kHostScalars doubles at host_scal (device) to host (mapped pinned
+    // memory) and then writes host_seq behind them.  host = NULL: none.
+    double* host = nullptr;
+    const double* host_scal = nullptr;
+    uint64_t host_seq = 0;
     int aug = 0;           // 1: s is [[0, R^T], [R, 0]] (J = 2 J_R): its leading J_R
                            // eigenvalues are sigma_i(R); lambda (J_R values) and the
                            // rank rule use sigma_i^2, u receives 2 J_R x R vectors
