@@ -2,165 +2,23 @@
 // computed in the natural layout without permuting data (Sec. V-C, local
 // part), exploiting symmetry: only 16x16 blocks (bi <= bj) are formed.
 //
-// Stage 1 (gram_partial_f64): workgroup (p, g) streams its contiguous range
-// of column tiles (TileMap) through a double-buffered LDS tile and
-// accumulates the block pairs of pair group g in registers.  Each wave owns
-// NPW block pairs (a compile-time count, so the MFMA loop is branch-free)
-// and a k-slice of each tile.  One barrier per tile: while the MFMAs read
-// buffer t % 2 the registers holding tile t + 1 are written to the other
-// buffer.  It writes one partial per pair to the workspace.
+// Stage 1 (gram_partial_f64; above extent 256 gram_partial_wide): a workgroup
+// streams its contiguous range of column tiles (TileMap) through a
+// double-buffered LDS tile and accumulates block pairs in registers.  Each
+// wave owns a compile-time set of pairs (GramSched) and a k-slice of each
+// tile.  One barrier per tile: while the MFMAs read buffer t % 2 the
+// registers holding tile t + 1 are written to the other buffer.  It writes
+// one partial per pair to the workspace.
 // Stage 2 (gram_reduce): sums the partials over p in a fixed order (so S is
 // bitwise reproducible) and mirrors the upper blocks into both triangles.
 //
 // FP64 path: v_mfma_f64_16x16x4f64 on FP64 data (FP32 input is widened
 // exactly while staging).  Narrow modes (J <= 32 over long contiguous runs)
 // replace stage 1 by gram_narrow_f64, which needs no LDS tile.
-#include "tile_io.hpp"
+#include "gram_f64.hpp"
 #include "tk_common.hpp"
 
 namespace tk {
-
-typedef double d4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kGramThreads = 512;
-constexpr int kGramWaves = kGramThreads / 64;
-
-// Pair index p -> (bi, bj), upper-triangle blocks in row-major order.
-__device__ __forceinline__ void pair_of(int p, int nb, int& bi, int& bj) {
-    int row = 0;
-    int start = 0;
-    while (p >= start + (nb - row)) {
-        start += nb - row;
-        ++row;
-    }
-    bi = row;
-    bj = row + (p - start);
-}
-
-// LDS doubles: two [JB][KT + 1] tile buffers (at least the area used to fold
-// k-slices at the end).
-template <int JB, int KT, int NPW>
-constexpr int kGramLdsDoubles = 2 * JB * (KT + 1) > kGramWaves * NPW * 256
-                                    ? 2 * JB * (KT + 1)
-                                    : kGramWaves * NPW * 256;
-
-// NPW: block pairs per wave; KS: waves sharing one pair set, each taking
-// every KS-th k-step.  The waves form kGramWaves / KS groups of NPW pairs.
-// One workgroup's share: tiles [t0, t1) of pair group g0 .. g0 + npg - 1;
-// writes npairs * 256 partial sums at `out` (those of its own pairs).
-template <typename T, int JB, int KT, int NPW, int KS, bool SKIP = false>
-__device__ __forceinline__ void gram_f64_body(const T* __restrict__ y, const TileMap& tm, int nb,
-                                              int g0, int npg, int64_t t0, int64_t t1,
-                                              double* __restrict__ out, double* lds) {
-    constexpr int P = KT + 1;
-    constexpr int NG = kGramWaves / KS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r16 = lane & 15, k4 = lane >> 4;
-
-    for (int e = tid; e < 2 * JB * P; e += kGramThreads) lds[e] = 0.0;
-
-    const int grp = wave % NG, slice = wave / NG;
-    // SKIP (batches, J below the extent class): pairs with a block at or past
-    // ceil(J / 16) sum zeros only and skip their products (partials stay 0)
-    const int nbv = SKIP ? __builtin_amdgcn_readfirstlane((tm.J + 15) >> 4) : nb;
-    int aoff[NPW], boff[NPW];
-    bool live[NPW];
-#pragma unroll
-    for (int q = 0; q < NPW; ++q) {
-        int p = g0 + min(grp * NPW + q, npg - 1);  // spare slots repeat the last pair
-        int bi, bj;
-        pair_of(p, nb, bi, bj);
-        live[q] = !SKIP || max(bi, bj) < nbv;
-        aoff[q] = (bi * 16 + r16) * P + k4;
-        boff[q] = (bj * 16 + r16) * P + k4;
-    }
-    d4_t acc[NPW];
-#pragma unroll
-    for (int q = 0; q < NPW; ++q) acc[q] = d4_t{0.0, 0.0, 0.0, 0.0};
-
-    ColumnTile<T, double, JB, KT, kGramThreads> ld;
-    ld.setup(tm, tid);
-    if (t0 < t1) ld.load(y, tm, tile_at(tm, t0, tm.J));
-    __syncthreads();  // zeroing done before the first store
-    if (t0 < t1) ld.store(lds);
-    __syncthreads();
-    for (int64_t t = t0; t < t1; ++t) {
-        const double* cur = lds + ((t - t0) & 1) * (JB * P);
-        double* nxt = lds + (((t - t0) + 1) & 1) * (JB * P);
-        const bool more = t + 1 < t1;
-        if (more) ld.load(y, tm, tile_at(tm, t + 1, tm.J));  // in flight during the MFMAs
-#pragma unroll
-        for (int kq = 0; kq < KT / 4 / KS; ++kq) {
-            const int ks = kq * KS + slice;
-            double a[NPW], b[NPW];
-#pragma unroll
-            for (int q = 0; q < NPW; ++q) {
-                a[q] = cur[aoff[q] + ks * 4];
-                b[q] = cur[boff[q] + ks * 4];
-            }
-#pragma unroll
-            for (int q = 0; q < NPW; ++q) {
-                if (SKIP && !live[q]) continue;  // uniform
-                acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], b[q], acc[q], 0, 0, 0);
-            }
-        }
-        if (more) ld.store(nxt);
-        __syncthreads();
-    }
-
-    // v_mfma_f64_16x16x4f64 leaves D[row][col] in lane col + 16 * (row % 4),
-    // register row / 4, i.e. row = 4 * v + lane / 16, col = lane % 16.
-    if constexpr (KS > 1) {
-        double* red = lds;  // [wave][NPW][256]
-#pragma unroll
-        for (int q = 0; q < NPW; ++q)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                red[(wave * NPW + q) * 256 + (4 * v + k4) * 16 + r16] = acc[q][v];
-        __syncthreads();
-        if (slice == 0) {
-#pragma unroll
-            for (int q = 0; q < NPW; ++q) {
-                int pl = grp * NPW + q;
-                if (pl < npg) {
-                    for (int e = lane; e < 256; e += 64) {
-                        double s = 0.0;
-#pragma unroll
-                        for (int sl = 0; sl < KS; ++sl)
-                            s += red[((sl * NG + grp) * NPW + q) * 256 + e];
-                        out[(int64_t)(g0 + pl) * 256 + e] = s;
-                    }
-                }
-            }
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < NPW; ++q) {
-            int pl = grp * NPW + q;
-            if (pl < npg) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    out[(int64_t)(g0 + pl) * 256 + (4 * v + k4) * 16 + r16] = acc[q][v];
-            }
-        }
-    }
-}
-
-// P tile ranges x G pair groups, one workgroup each (xcd_range_group).
-template <typename T, int JB, int KT, int NPW, int KS>
-__global__ __launch_bounds__(kGramThreads) void gram_partial_f64(
-    const T* __restrict__ y, TileMap tm, int nb, int npairs, int pairs_per_group, int P, int G,
-    double* __restrict__ partial) {
-    extern __shared__ double lds[];
-    int p, g;
-    xcd_range_group(blockIdx.x, G, p, g);
-    const int g0 = g * pairs_per_group;
-    const int npg = min(npairs - g0, pairs_per_group);
-    const int64_t t0 = tm.ntiles * (int64_t)p / P;
-    const int64_t t1 = tm.ntiles * (int64_t)(p + 1) / P;
-    gram_f64_body<T, JB, KT, NPW, KS>(y, tm, nb, g0, npg, t0, t1,
-                                      partial + (int64_t)p * npairs * 256, lds);
-}
 
 // acc + partial[q n + idx] over q = g, g + 4, ... < P, added in that order;
 // eight loads go out per trip so that they overlap.
@@ -367,37 +225,6 @@ __global__ __launch_bounds__(kNarrowThreads) void gram_narrow_f64(
 
 // ------------------------------------------------------------------ host
 
-static int round_jb(int J) {
-    int jb = 32;
-    while (jb < J) jb *= 2;
-    return jb;
-}
-
-// Static schedule per padded extent: tile width, pairs per wave, k-slices
-// per pair set, and pairs per workgroup group.
-struct GramShape {
-    int KT, NPW, KS, per_group;
-};
-
-template <int JB>
-constexpr GramShape gram_shape() {
-    return JB == 32    ? GramShape{32, 1, 2, 4}    //   3 pairs: 4 groups x 1, 2 k-slices
-           : JB == 64  ? GramShape{32, 3, 2, 12}   //  10 pairs: 4 groups x 3, 2 k-slices
-           : JB == 128 ? GramShape{32, 5, 1, 40}   //  36 pairs: 8 waves x 5
-           : JB == 256 ? GramShape{32, 6, 1, 48}   // 136 pairs: 3 groups of <= 48
-                       : GramShape{16, 8, 1, 64};  // 528 pairs: 9 groups of <= 64
-}
-
-static GramShape gram_shape_rt(int jb) {
-    switch (jb) {
-        case 32: return gram_shape<32>();
-        case 64: return gram_shape<64>();
-        case 128: return gram_shape<128>();
-        case 256: return gram_shape<256>();
-        default: return gram_shape<512>();
-    }
-}
-
 // Narrow-mode plan: one partial per workgroup, at most 2 per CU, each
 // workgroup holding at least one batch of steps per wave.
 constexpr int kNarrowStepsF32 = 4, kNarrowStepsF64 = 2;  // U: steps per batch
@@ -423,14 +250,25 @@ static GramPlan plan_narrow(const ModeView& v, int elem_bytes) {
 
 static GramPlan plan_tiled(const ModeView& v) {
     GramPlan pl{};
-    GramShape gs = gram_shape_rt(round_jb(v.J));
-    pl.KT = gs.KT;
     pl.nb = (v.J + 15) / 16;
     pl.npairs = pl.nb * (pl.nb + 1) / 2;
-    pl.G = (pl.npairs + gs.per_group - 1) / gs.per_group;
+    int64_t want = device_cu_count();
+    if (pl.nb <= 16) {
+        pl.G = 1;
+        with_blocks(pl.nb, [&](auto nbc) {
+            typedef GramSched<decltype(nbc)::value> S;
+            pl.KT = S::KT;
+            want *= S::kPerCu;
+            return (int)TK_OK;
+        });
+    } else {
+        pl.KT = kWideKt;
+        pl.G = (pl.npairs + kWidePairs - 1) / kWidePairs;
+        want /= pl.G;
+    }
     pl.pairs_per_group = (pl.npairs + pl.G - 1) / pl.G;
     TileMap tm = make_tiles(v, pl.KT);
-    const int64_t want = xcd_round_want((int64_t)2 * device_cu_count() / pl.G, pl.G);
+    want = xcd_round_want(want, pl.G);
     pl.P = xcd_ranges(tm.ntiles, want, pl.G);
     pl.partial_bytes = (size_t)pl.P * pl.npairs * 256 * sizeof(double);
     pl.partial_bound = (size_t)want * pl.npairs * 256 * sizeof(double);
@@ -467,36 +305,8 @@ static int dispatch_narrow(const T* y, const ModeView& v, const GramPlan& pl, do
                            : launch_narrow<T, 32>(y, v, pl, partial, st);
 }
 
-template <typename T, int JB>
-static int launch_partial(const T* y, const TileMap& tm, const GramPlan& pl, double* partial,
-                          hipStream_t st) {
-    constexpr GramShape gs = gram_shape<JB>();
-    size_t lds = (size_t)kGramLdsDoubles<JB, gs.KT, gs.NPW> * sizeof(double);
-    auto fn = gram_partial_f64<T, JB, gs.KT, gs.NPW, gs.KS>;
-    TK_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds));
-    hipLaunchKernelGGL(fn, dim3(pl.P * pl.G), dim3(kGramThreads), lds, st, y, tm, pl.nb,
-                       pl.npairs, pl.pairs_per_group, pl.P, pl.G, partial);
-    TK_HIP(hipGetLastError());
-    return TK_OK;
-}
-
-template <typename T>
-static int dispatch_partial(const T* y, const ModeView& v, const GramPlan& pl, double* partial,
-                            hipStream_t st) {
-    TileMap tm = make_tiles(v, pl.KT);
-    switch (round_jb(v.J)) {
-        case 32: return launch_partial<T, 32>(y, tm, pl, partial, st);
-        case 64: return launch_partial<T, 64>(y, tm, pl, partial, st);
-        case 128: return launch_partial<T, 128>(y, tm, pl, partial, st);
-        case 256: return launch_partial<T, 256>(y, tm, pl, partial, st);
-        case 512: return launch_partial<T, 512>(y, tm, pl, partial, st);
-        default: return fail(TK_ERR_UNSUPPORTED, "mode extent %d exceeds %d", v.J, TK_MAX_MODE_DIM);
-    }
-}
-
-int launch_gram_reduce(const double* partial, const GramPlan& pl, int J, double* s,
-                       const double* aux, double* stats, hipStream_t st) {
+static int launch_gram_reduce(const double* partial, const GramPlan& pl, int J, double* s,
+                              const double* aux, double* stats, hipStream_t st) {
     int n = pl.npairs * 256;
     const int nblk = (n + 63) / 64 + (aux ? 1 : 0);
     hipLaunchKernelGGL(gram_reduce, dim3(nblk), dim3(256), 0, st, partial, pl.P, pl.npairs,
@@ -594,49 +404,6 @@ int launch_gram_reduce_batched(const BatchReduceTask* tasks_dev, int ntasks, int
     return TK_OK;
 }
 
-// FP64 Gram of every problem of a batch (the guard's recomputation when
-// `conditional`).  The partials use the split kernel's layout -- 16-blocks of
-// the padded extent JB, pairs in pair_of order -- so the same reduction
-// tasks apply; pairs in the padding come out zero.
-template <int JB>
-__global__ __launch_bounds__(kGramThreads) void gram_f64_batched(
-    const BatchGramTask* __restrict__ tasks, int ntasks, int conditional) {
-    extern __shared__ double lds[];
-    constexpr GramShape gs = gram_shape<JB>();
-    constexpr int nb = JB / 16, npairs = nb * (nb + 1) / 2;
-    static_assert(gs.per_group >= npairs, "batches need a single pair group");
-    const int ti = find_task_wg(&tasks[0].v, sizeof(BatchGramTask), ntasks, blockIdx.x);
-    BatchGramTask tk = tasks[ti];
-    tk.y = uni_global(tk.y);  // global, not flat, accesses
-    tk.partial = uni_global(tk.partial);
-    // uniform over the workgroup: 1 = the redo of uncertain ranks (bit 4),
-    // 2 = the problems marked FP64-only (bit 8)
-    if (conditional && !(*tk.status & (conditional == 2 ? 8 : 4))) return;
-    const int w = blockIdx.x - tk.v.wg_begin;
-    const TileMap tm = make_tiles(batch_mode_view(tk.v), gs.KT);
-    const int active = (int)(tm.ntiles < tk.v.nwg ? tm.ntiles : tk.v.nwg);
-    if (w == 0 && threadIdx.x == 0) *tk.nparts = active;
-    if (w >= active) return;  // uniform over the workgroup
-    const int64_t t0 = tm.ntiles * (int64_t)w / active;
-    const int64_t t1 = tm.ntiles * (int64_t)(w + 1) / active;
-    gram_f64_body<float, JB, gs.KT, gs.NPW, gs.KS, true>(
-        tk.y, tm, nb, 0, npairs, t0, t1, tk.partial + (int64_t)w * npairs * 256, lds);
-}
-
-template <int JB>
-static int launch_f64_batched_t(const BatchGramTask* tasks, int ntasks, int total_wg,
-                                int conditional, hipStream_t st) {
-    constexpr GramShape gs = gram_shape<JB>();
-    const size_t lds = (size_t)kGramLdsDoubles<JB, gs.KT, gs.NPW> * sizeof(double);
-    auto fn = gram_f64_batched<JB>;
-    TK_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)lds));
-    hipLaunchKernelGGL(fn, dim3(total_wg), dim3(kGramThreads), lds, st, tasks, ntasks,
-                       conditional);
-    TK_HIP(hipGetLastError());
-    return TK_OK;
-}
-
 // One thread per task: the problem's FP64 Gram work at its actual shape
 // (the truncated extents come from the device ranks) decides bit 8.
 __global__ __launch_bounds__(64) void batch_mark_fp64(const BatchGramTask* __restrict__ tasks,
@@ -658,16 +425,6 @@ int launch_batch_mark_fp64(const BatchGramTask* tasks_dev, int ntasks, double ma
     return TK_OK;
 }
 
-int launch_gram_f64_batched(const BatchGramTask* tasks_dev, int ntasks, int total_wg, int jb,
-                            int conditional, hipStream_t st) {
-    switch (jb) {
-        case 32: return launch_f64_batched_t<32>(tasks_dev, ntasks, total_wg, conditional, st);
-        case 64: return launch_f64_batched_t<64>(tasks_dev, ntasks, total_wg, conditional, st);
-        case 128: return launch_f64_batched_t<128>(tasks_dev, ntasks, total_wg, conditional, st);
-        default: return fail(TK_ERR_UNSUPPORTED, "batched FP64 Gram: extent class %d", jb);
-    }
-}
-
 int launch_gram(const void* y, int dtype, const ModeView& v, int precision, double* s,
                 double* sumsq, void* ws, size_t ws_bytes, hipStream_t st,
                 double* split_stats, const hipEvent_t* ev) {
@@ -686,9 +443,9 @@ int launch_gram(const void* y, int dtype, const ModeView& v, int precision, doub
         else
             TK_TRY(dispatch_narrow((const float*)y, v, pl, partial, st));
     } else if (dtype == TK_F64) {
-        TK_TRY(dispatch_partial((const double*)y, v, pl, partial, st));
+        TK_TRY(launch_gram_f64((const double*)y, v, pl, partial, st));
     } else {
-        TK_TRY(dispatch_partial((const float*)y, v, pl, partial, st));
+        TK_TRY(launch_gram_f64((const float*)y, v, pl, partial, st));
     }
     if (ev) TK_HIP(hipEventRecord(ev[1], st));
     const bool split = precision == TK_GRAM_SPLIT_BF16;
