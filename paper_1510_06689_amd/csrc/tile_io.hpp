@@ -2,8 +2,9 @@
 //
 // A tile is J x KT columns of the block-column view Y[B][J][L] (TileMap).
 // ColumnTile loads one tile into registers with a thread mapping that keeps
-// every wave's global loads contiguous, widens to the compute type, and
-// writes it to LDS as [i][kk] with a row pitch of KT + 1 elements (an odd
+// every wave's global loads contiguous, and writes it to LDS, widened to the
+// compute type (a conversion at the load would wait for the data), as
+// [i][kk] with a row pitch of KT + 1 elements (an odd
 // pitch in 8-byte words spreads both the row-wise and the column-wise
 // accesses across banks).
 //   L == 1 : column kk is J contiguous elements -> thread t reads row
@@ -31,7 +32,7 @@ struct ColumnTile {
     static_assert(THREADS % JB == 0 && THREADS % KT == 0, "thread mappings need JB, KT | THREADS");
     static constexpr int kPer = JB * KT / THREADS;
     static constexpr int P = KT + 1;  // LDS row pitch (elements)
-    C v[kPer];
+    T v[kPer];
     int64_t coff;  // L > 1: offset of this thread's column
     int kk0, i0;   // this thread's first (i, kk)
     bool unit;     // L == 1
@@ -56,8 +57,8 @@ struct ColumnTile {
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
                 int kk = kk0 + q * colstep;
-                C val = C(0);
-                if (i0 < tm.J && kk < t.ncols) val = (C)y[t.base + (int64_t)kk * tm.J + i0];
+                T val = T(0);
+                if (i0 < tm.J && kk < t.ncols) val = y[t.base + (int64_t)kk * tm.J + i0];
                 v[q] = val;
             }
         } else {
@@ -65,8 +66,8 @@ struct ColumnTile {
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
                 int i = i0 + q * rowstep;
-                C val = C(0);
-                if (i < tm.J && kk0 < t.ncols) val = (C)y[t.base + coff + (int64_t)i * tm.L];
+                T val = T(0);
+                if (i < tm.J && kk0 < t.ncols) val = y[t.base + coff + (int64_t)i * tm.L];
                 v[q] = val;
             }
         }
@@ -76,11 +77,11 @@ struct ColumnTile {
         if (unit) {
             constexpr int colstep = THREADS / JB;
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) lds[i0 * P + kk0 + q * colstep] = v[q];
+            for (int q = 0; q < kPer; ++q) lds[i0 * P + kk0 + q * colstep] = (C)v[q];
         } else {
             constexpr int rowstep = THREADS / KT;
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) lds[(i0 + q * rowstep) * P + kk0] = v[q];
+            for (int q = 0; q < kPer; ++q) lds[(i0 + q * rowstep) * P + kk0] = (C)v[q];
         }
     }
 };

@@ -17,10 +17,9 @@
 // whatever precision is asked for.
 #include "tile_io.hpp"
 #include "tk_common.hpp"
+#include "ttm_f64.hpp"
 
 namespace tk {
-
-typedef double d4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTtmThreads = 512;
 constexpr int kTtmWaves = kTtmThreads / 64;
@@ -306,6 +305,14 @@ static int pick_kb(const T* y, const ModeView& v, const double* m, int64_t ldm, 
 template <typename T>
 static int dispatch_ttm(const T* y, const ModeView& v, const double* m, int64_t K, int64_t ldm,
                         int transpose, T* z, hipStream_t st) {
+    // Many output rows of a wide mode are product-bound: the operator goes to
+    // registers there.  J = 128, K = 64: 0.39 -> 0.33 ms (FP64, 0.8 GB), FP32
+    // 0.63 -> 0.31; J = 250, K = 100: 140 -> 94 us.  Up to K = 32 or J = 64 the
+    // tensor's bytes take longer and the kernel below, which starts faster and
+    // keeps more loads under way, is ahead (J = 64, K = 48 FP64: 73 against 86
+    // us; J = 128, K = 20, 26 MB: 15 against 18 us).
+    if (K > 32 && v.J > 64 && v.J <= 256)
+        return launch_ttm_reg(y, v, m, ldm, (int)K, transpose, z, st);
     switch (round_pow2(v.J, 32)) {
         case 32: return pick_kb<T, 32>(y, v, m, ldm, (int)K, transpose, z, st);
         case 64: return pick_kb<T, 64>(y, v, m, ldm, (int)K, transpose, z, st);
