@@ -1242,6 +1242,33 @@ int launch_gram_mixed(const float* y, const ModeView& v, const GramPlan& pl, dou
 constexpr int kMtThreads = 256;
 constexpr int kMtWaves = kMtThreads / 64;
 
+// Rows [r0, r0 + 16 nkb) of op(M) as bf16 fragments: lane l of fragment
+// kb * NKS + ks holds op(M)[r0 + 16 kb + l % 16][32 ks + 8 (l / 16) + e], its
+// high half at entry 2 f and the rest at 2 f + 1.  All threads.
+template <int NKS>
+__device__ __forceinline__ void stage_op_bf16(const double* __restrict__ m, int64_t ldm, int K,
+                                              int J, int transpose, int r0, int nkb,
+                                              bf8_t (*afr)[64]) {
+    for (int f = threadIdx.x; f < nkb * NKS * 64; f += kMtThreads) {
+        const int l = f & 63, kbks = f >> 6;
+        const int kb = kbks / NKS, ks = kbks - (kbks / NKS) * NKS;
+        const int r = r0 + 16 * kb + (l & 15);
+        bf8_t h, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int j = 32 * ks + 8 * (l >> 4) + e;
+            double a = 0.0;
+            if (r < K && j < J) a = transpose ? m[j + ldm * r] : m[r + ldm * j];
+            const float af = (float)a;
+            const __bf16 ah = (__bf16)af;
+            h[e] = ah;
+            lo[e] = (__bf16)(af - (float)ah);
+        }
+        afr[kbks * 2][l] = h;
+        afr[kbks * 2 + 1][l] = lo;
+    }
+}
+
 // NKB: 16-row blocks of op(M) per workgroup; NKS: 32-wide k-steps over J;
 // X3: split both operands (three products) instead of one bf16 product.
 // UNIT: L == 1, each column's J floats contiguous: a lane's 8 rows of a
@@ -1260,25 +1287,7 @@ __device__ __forceinline__ void ttm_bf16_body(
     bf8_t (*afr)[64]) {
     const int tid = threadIdx.x, lane = tid & 63;
 
-    // A fragments: lane l holds op(M)[r0 + 16 kb + l % 16][32 ks + 8 (l / 16) + e].
-    for (int f = tid; f < NKB * NKS * 64; f += kMtThreads) {
-        const int l = f & 63, kbks = f >> 6;
-        const int kb = kbks / NKS, ks = kbks - (kbks / NKS) * NKS;
-        const int r = r0 + 16 * kb + (l & 15);
-        bf8_t h, lo;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int j = 32 * ks + 8 * (l >> 4) + e;
-            double a = 0.0;
-            if (r < K && j < J) a = transpose ? m[j + ldm * r] : m[r + ldm * j];
-            const float af = (float)a;
-            const __bf16 ah = (__bf16)af;
-            h[e] = ah;
-            lo[e] = (__bf16)(af - (float)ah);
-        }
-        afr[kbks * 2][l] = h;
-        afr[kbks * 2 + 1][l] = lo;
-    }
+    stage_op_bf16<NKS>(m, ldm, K, J, transpose, r0, NKB, afr);
     __syncthreads();
 
     const int c16 = lane & 15, g4 = lane >> 4;
@@ -1369,6 +1378,97 @@ __global__ __launch_bounds__(kMtThreads) void ttm_bf16_kernel(
                                       blockIdx.y * NKB * 16, blockIdx.x, gridDim.x, afr);
 }
 
+// The same product where the rows are runs of L columns, L a multiple of 4 and
+// at least 16, and both pointers 16-byte aligned: lane c16 of a wave takes
+// columns 4 c16 .. 4 c16 + 3 of 64, as column c16 of four MFMA column blocks,
+// so that every row of Y is read, and every row of Z written, 16 bytes a lane
+// and 256 bytes a quarter-wave.  (One block of 16 columns at a time touched 64
+// bytes of a row: an expansion from 16 to 128 rows, 8.6 GB written, took 4.09
+// ms against 1.93 here, 5.0 TB/s; 128 to 16 rows of 64 x 128 x 32 x 8 columns
+// 57 against 52 us.)  The wave's part of Y stays in registers for
+// all row blocks, so Y is read once whatever K is.  Every output's products
+// and their order are those of ttm_bf16_kernel.
+template <int NKS, bool X3>
+__global__ __launch_bounds__(kMtThreads) void ttm_bf16_quad(
+    const float* __restrict__ y, int64_t L, int64_t ncols, int J, const double* __restrict__ m,
+    int64_t ldm, int K, int transpose, float* __restrict__ z, int group_kb) {
+    extern __shared__ bf8_t afq[][64];  // [(kb * NKS + ks) * 2 + hi/lo][lane]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int r0 = (int)blockIdx.y * group_kb * 16;
+    const int nkb = min(group_kb, (K - r0 + 15) / 16);
+    stage_op_bf16<NKS>(m, ldm, K, J, transpose, r0, nkb, afq);
+    __syncthreads();
+
+    const int c16 = lane & 15, g4 = lane >> 4;
+    const int64_t nblk = (ncols + 63) / 64;
+    const int64_t wstride = (int64_t)gridDim.x * kMtWaves;
+    int64_t cb = (int64_t)blockIdx.x * kMtWaves + __builtin_amdgcn_readfirstlane(tid >> 6);
+    // block b and column l of the wave's first column, advanced without division
+    int64_t b0 = cb * 64 / L, l0 = cb * 64 - b0 * L;
+    const int64_t db = wstride * 64 / L, dl = wstride * 64 - db * L;
+    const int64_t JL = (int64_t)J * L, KL = (int64_t)K * L;
+    for (; cb < nblk; cb += wstride) {
+        int64_t b = b0, l = l0 + 4 * c16;
+        while (l >= L) {
+            l -= L;
+            ++b;
+        }
+        const bool cv = cb * 64 + 4 * c16 < ncols;  // ncols is a multiple of 4
+        const float* ycol = y + b * JL + l;
+        bf8_t yh[NKS][4], yl[NKS][4];
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            const int j0 = 32 * ks + 8 * g4;
+            f4_t x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                x[e] = (cv && j0 + e < J)
+                           ? *reinterpret_cast<const f4_t*>(ycol + (int64_t)(j0 + e) * L)
+                           : f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const __bf16 h = (__bf16)x[e][q];
+                    yh[ks][q][e] = h;
+                    if (X3) yl[ks][q][e] = (__bf16)(x[e][q] - (float)h);
+                }
+        }
+        float* zc = z + b * KL + l;
+        for (int kb = 0; kb < nkb; ++kb) {
+            f4_t acc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = f4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                const bf8_t ah = afq[(kb * NKS + ks) * 2][lane];
+                const bf8_t al = X3 ? afq[(kb * NKS + ks) * 2 + 1][lane] : ah;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, yh[ks][q], acc[q], 0, 0, 0);
+                    if (X3) {
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, yl[ks][q], acc[q], 0, 0, 0);
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, yh[ks][q], acc[q], 0, 0, 0);
+                    }
+                }
+            }
+            // row 4 (lane / 16) + v, the lane's four columns
+            const int rb = r0 + 16 * kb + 4 * g4;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (cv && rb + v < K)
+                    *reinterpret_cast<f4_t*>(zc + (int64_t)(rb + v) * L) =
+                        f4_t{acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
+        }
+        b0 += db;
+        l0 += dl;
+        if (l0 >= L) {
+            l0 -= L;
+            ++b0;
+        }
+    }
+}
+
 template <int NKB, int NKS, bool X3>
 static int mt_launch(const float* y, const ModeView& v, const double* m, int64_t ldm, int K,
                      int transpose, float* z, hipStream_t st) {
@@ -1405,10 +1505,41 @@ static int mt_pick_kb(const float* y, const ModeView& v, const double* m, int64_
     return fail(TK_ERR_UNSUPPORTED, "bf16 ttm: no tile for K=%d", K);
 }
 
+template <int NKS, bool X3>
+static int mt_launch_quad(const float* y, const ModeView& v, const double* m, int64_t ldm, int K,
+                          int transpose, float* z, hipStream_t st) {
+    const int64_t ncols = v.L * v.B;
+    const int need = (K + 15) / 16;
+    const int kb = std::min(need, 32 / NKS);  // at most 64 KB of fragments
+    const int G = (need + kb - 1) / kb;
+    const size_t lds = (size_t)kb * NKS * 2 * 64 * sizeof(bf8_t);
+    auto fn = ttm_bf16_quad<NKS, X3>;
+    TK_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)lds));
+    int per_cu = 1;
+    TK_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)fn, kMtThreads, lds));
+    if (per_cu < 1) per_cu = 1;
+    const int64_t want = ((int64_t)per_cu * device_cu_count() + G - 1) / G;
+    const int64_t P = std::min(want, ((ncols + 63) / 64 + kMtWaves - 1) / kMtWaves);
+    if (P < 1) return TK_OK;
+    hipLaunchKernelGGL(fn, dim3((unsigned)P, G), dim3(kMtThreads), lds, st, y, v.L, ncols, v.J, m,
+                       ldm, K, transpose, z, kb);
+    TK_HIP(hipGetLastError());
+    return TK_OK;
+}
+
 template <bool X3>
 static int mt_dispatch(const float* y, const ModeView& v, const double* m, int64_t ldm, int K,
                        int transpose, float* z, hipStream_t st) {
     const int nks = (v.J + 31) / 32;
+    if (v.L % 4 == 0 && v.L >= 16 && nks <= 4 && (uintptr_t)y % 16 == 0 && (uintptr_t)z % 16 == 0) {
+        switch (nks) {
+            case 1: return mt_launch_quad<1, X3>(y, v, m, ldm, K, transpose, z, st);
+            case 2: return mt_launch_quad<2, X3>(y, v, m, ldm, K, transpose, z, st);
+            case 3: return mt_launch_quad<3, X3>(y, v, m, ldm, K, transpose, z, st);
+            default: return mt_launch_quad<4, X3>(y, v, m, ldm, K, transpose, z, st);
+        }
+    }
     if (nks <= 1) return mt_pick_kb<1, X3>(y, v, m, ldm, K, transpose, z, st);
     if (nks <= 2) return mt_pick_kb<2, X3>(y, v, m, ldm, K, transpose, z, st);
     if (nks <= 3) return mt_pick_kb<3, X3>(y, v, m, ldm, K, transpose, z, st);
