@@ -39,6 +39,18 @@ __device__ __forceinline__ double qr_wave_sum(double v) {
     return v;
 }
 
+// 1/q and 1/sqrt(s) (s > 0) from the hardware estimates and Newton steps.
+__device__ __forceinline__ double qr_recip(double q) {
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(r, fma(-q, r, 1.0), r);
+    return fma(r, fma(-q, r, 1.0), r);
+}
+__device__ __forceinline__ double qr_rsq(double s) {
+    double r = __builtin_amdgcn_rsq(s);
+    r = fma(0.5 * r, fma(-(s * r), r, 1.0), r);
+    return fma(0.5 * r, fma(-(s * r), r, 1.0), r);
+}
+
 // Cross-lane exchanges on VALU (no LDS round trip):
 //   offset 32: v_permlane32_swap(a, b) -> ([a 0-31, b 0-31], [a 32-63, b 32-63]),
 //   offset 16: v_permlane16_swap(a, b) -> (even rows of a, b; odd rows of a, b),
@@ -170,11 +182,14 @@ __device__ __forceinline__ void make_reflector(const double (&col)[RPL], int k, 
     const double alpha = Rs[k * JC + k];
     double tau = 0.0, scal = 0.0;
     if (xn2 > 0.0) {
-        const double nrm = sqrt(fma(alpha, alpha, xn2));
-        const double beta = alpha >= 0.0 ? -nrm : nrm;
-        tau = (beta - alpha) / beta;
-        scal = 1.0 / (alpha - beta);
-        if (lane == 0) Rs[k * JC + k] = beta;
+        // one reciprocal square root and one reciprocal, refined, instead of
+        // a square root and two divisions: the other waves wait for this
+        const double ss = fma(alpha, alpha, xn2);
+        const double rs = qr_rsq(ss);
+        const double nrm = ss * rs;
+        tau = fma(fabs(alpha), rs, 1.0);
+        scal = (alpha >= 0.0 ? 1.0 : -1.0) * qr_recip(fabs(alpha) + nrm);
+        if (lane == 0) Rs[k * JC + k] = alpha >= 0.0 ? -nrm : nrm;
     }
 #pragma unroll
     for (int p = 0; p < RPL; ++p) vbuf[lane + 64 * p] = col[p] * scal;
@@ -293,7 +308,9 @@ __device__ __forceinline__ void absorb_from(double (&a)[QrGeom<JC>::RPL][QrGeom<
 }
 
 // One level of the reduction.  Workgroup g absorbs rows
-// [g * rows_per_wg, min(rows, (g + 1) * rows_per_wg)) of src.  Unless r_final
+// [g * rows_per_wg, min(rows, (g + 1) * rows_per_wg)) of src; with seed (a
+// later level: src stacks partial factors, J rows each) the first factor of
+// them is taken over as the running R instead.  Unless r_final
 // is set it writes its R (column-major JC x JC, zero below the diagonal) to
 // r_part + g JC^2 and, when ss_part is set, the sum of squares of its rows to
 // ss_part[g].  With r_final (one workgroup) it writes R as column-major J x J
@@ -301,6 +318,7 @@ __device__ __forceinline__ void absorb_from(double (&a)[QrGeom<JC>::RPL][QrGeom<
 // of ss_in[0 .. n_ss_in) in index order (or of its own rows if ss_in is NULL).
 template <int JC>
 __global__ __launch_bounds__(kQrThreads) void tsqr_kernel(QrSrc src, int J, int64_t rows_per_wg,
+                                                          int seed,
                                                           double* __restrict__ r_part,
                                                           double* __restrict__ ss_part,
                                                           double* __restrict__ r_final,
@@ -319,9 +337,18 @@ __global__ __launch_bounds__(kQrThreads) void tsqr_kernel(QrSrc src, int J, int6
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     double* wb = wbuf + wave * CPW;
 
-    for (int i = tid; i < JC * JC; i += kQrThreads) Rs[i] = 0.0;
-    const int64_t r_begin = (int64_t)blockIdx.x * rows_per_wg;
+    int64_t r_begin = (int64_t)blockIdx.x * rows_per_wg;
     const int64_t r_end = min(r_begin + rows_per_wg, src.rows);
+    if (seed) {  // uniform; src is a previous level's factors, column-major JC x JC
+        const double* f = (const double*)src.y + r_begin / J * src.sB;
+        for (int idx = tid; idx < JC * JC; idx += kQrThreads) {
+            const int j = idx / JC, i = idx - j * JC;
+            Rs[i * JC + j] = f[idx];
+        }
+        r_begin += J;
+    } else {
+        for (int i = tid; i < JC * JC; i += kQrThreads) Rs[i] = 0.0;
+    }
     double ss = 0.0;
     double a[RPL][CPW];
     __syncthreads();
@@ -521,9 +548,11 @@ QrPlan plan_qr(const ModeView& v) {
     pl.rows_per_wg[0] = tiles_per * pl.BR;
     pl.P[0] = (int)((rows + pl.rows_per_wg[0] - 1) / pl.rows_per_wg[0]);
     pl.levels = 1;
-    // later levels: each workgroup absorbs F partial factors (about four tiles of rows)
-    int F = 4 * pl.BR / v.J;
-    if (F < 2) F = 2;
+    // later levels: a workgroup takes over one partial factor and absorbs one
+    // tile's worth of others (a tile takes a fixed time, 128 steps at JC = 128;
+    // eight factors in four tiles, on a zero R, made the 256 leaves of a
+    // 2^18 x 128 matrix a tree of 1.67 ms, this one of 1.06 ms)
+    const int F = 1 + pl.BR / v.J;
     while (pl.P[pl.levels - 1] > 1) {
         const int prev = pl.P[pl.levels - 1];
         pl.rows_per_wg[pl.levels] = (int64_t)F * v.J;
@@ -565,7 +594,7 @@ static int launch_tsqr_t(const void* y, int dtype, const ModeView& v, const QrPl
             src = QrSrc{prev, 0, (int64_t)pl.P[lv - 1] * v.J, v.J, (int64_t)JC * JC, JC};
         }
         hipLaunchKernelGGL(fn, dim3(pl.P[lv]), dim3(kQrThreads), lds, st, src, v.J,
-                           pl.rows_per_wg[lv], last ? nullptr : dst,
+                           pl.rows_per_wg[lv], lv > 0 ? 1 : 0, last ? nullptr : dst,
                            lv == 0 && !last ? ssp : nullptr, last ? r_out : nullptr,
                            last ? sumsq : nullptr, lv > 0 ? ssp : nullptr,
                            lv > 0 ? pl.P[0] : 0);
