@@ -125,7 +125,7 @@ size_t eig_scratch_doubles(int J) {
 }
 
 // small per-matrix arrays + the [C][rb] partial sums of the tridiagonal step
-static size_t eig_small_doubles(int J) { return (size_t)10 * J + 64 + 8 + (size_t)kEigThreads; }
+static size_t eig_small_doubles(int J) { return (size_t)8 * J + 64 + 8 + (size_t)kEigThreads; }
 
 // LDS doubles for the matrix (J <= 128) and later the inverse-iteration
 // batch; region + small arrays stay within the 160 KB of LDS.
@@ -136,48 +136,123 @@ static size_t eig_region_doubles(int J) {
     // room for every vector in one batch: a record of kLuArrays values per
     // padded row plus one, and two scale factors, per vector
     const size_t want = ((size_t)kLuArrays * eig_sweep_rows(J) + 3) * J;
-    return want < cap ? want : cap;
+    return (want < cap ? want : cap) & ~size_t(1);  // even: what follows holds 16-byte pairs
 }
 
 // Number of eigenvalues of the (scaled) tridiagonal matrix below x: sign
 // changes along the leading principal minors
 //   p_0 = 1,  p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2}.
-// An exactly zero minor is replaced by +2^-600: over that step and the next
-// one the number of sign changes is the same whichever sign a zero takes (it
-// is one), a zero last minor (x an eigenvalue) is correctly not counted, and
-// a zero followed by e_i = 0 restarts the next block from a tiny value.  The
-// pair (p_{i-1}, p_i) is rescaled by 2^+-300 every four steps (exact).
-__device__ __forceinline__ int sturm_count(const double* __restrict__ ds,
-                                           const double* __restrict__ e2s, int J, double x) {
-    constexpr double kUp = 0x1p300, kDown = 0x1p-300, kZero = 0x1p-600;
-    double p0 = 1.0, p1 = ds[0] - x;
-    p1 = p1 == 0.0 ? kZero : p1;
-    bool neg = p1 < 0.0;
-    int c = (int)neg;
-    auto step = [&](double di, double ei2) {
-        double p2 = fma(di - x, p1, -ei2 * p0);
-        p2 = p2 == 0.0 ? kZero : p2;
-        const bool n2 = p2 < 0.0;
-        c += (int)(n2 != neg);
-        neg = n2;
+// The squares are at least kMinE2 (scale_t raises smaller ones: a change of T
+// by 2^-70 of its norm), so an exactly zero minor is followed by one of the
+// opposite sign to its predecessor: one sign change over the two steps
+// whichever sign the zero takes, and nothing needs to replace it.
+//
+// What bounds it: a wave's own instructions, since a solve's few waves leave
+// SIMDs idle.  A step is three FP64 instructions, of which one fma is in the
+// chain, and one that shifts its sign into a word; signs are compared and
+// counted once per block of eight rows, and the pair (p_{i-1}, p_i) is
+// rescaled once per block (exact): it grows by less than 2^16 and, losing a
+// rounding and a smallest square every second step, shrinks by less than
+// 2^-780, so from 2^kTop it neither overflows nor vanishes.  Rows are read
+// a block ahead: through the scalar unit from the hand-off area in the split
+// solves (no vector instruction, no LDS; T is the same for every lane), from
+// LDS in the one-launch solver.  Both may read, and do not use, up to eight
+// rows behind the last one; what follows T in both places is longer.  One wave per eigenvalue, J = 128:
+// testing and counting every minor in floating point 50 us, in integers every
+// step with rows through LDS 42 us, this form 27 us (J = 301
+// 120, 100, 46).  Four rows ahead instead of eight left the scalar loads'
+// latency in sight: 34 us.
+constexpr double kMinE2 = 0x1p-140;
+constexpr double kSectTol = 2.0 * DBL_EPSILON;  // width of a found interval; T is scaled to norm <= 1
+struct TRows {
+    double d[8], e2[8];  // eight rows of T: d_i, e_{i-1}^2
+};
+
+struct LdsRows {
+    const double2* t;  // (d_i, e_{i-1}^2)
+    __device__ __forceinline__ void load(int i, TRows& q) const {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const double2 v = t[i + r];
+            q.d[r] = v.x;
+            q.e2[r] = v.y;
+        }
+    }
+    __device__ __forceinline__ void sent() const {}
+    __device__ __forceinline__ void arrive() const {}  // LDS returns in order: the compiler's waits do
+};
+
+struct ScalarRows {
+    using cdouble = const __attribute__((address_space(4))) double;
+    cdouble* t;  // pairs as above, written by an earlier launch
+    __device__ __forceinline__ explicit ScalarRows(const double* p)
+        : t(reinterpret_cast<cdouble*>(reinterpret_cast<uint64_t>(p))) {}
+    __device__ __forceinline__ void load(int i, TRows& q) const {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            q.d[r] = t[2 * (i + r)];
+            q.e2[r] = t[2 * (i + r) + 1];
+        }
+    }
+    // scalar loads return in any order, so a wait is for all of them: here,
+    // before the next ones go out
+    __device__ __forceinline__ void arrive() const {
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void sent() const { __builtin_amdgcn_sched_barrier(0); }
+};
+
+template <class Rows>
+__device__ __forceinline__ int sturm_count(const Rows& rows, double d0, int J, double x) {
+    constexpr int kTop = 800;
+    double p0 = 0x1p800, p1 = (d0 - x) * 0x1p800;
+    unsigned sg = (unsigned)__double2hiint(p1) >> 31;  // signs, the latest in bit 0
+    int c = (int)sg;
+    auto step = [&](const TRows& q, int r) {
+        const double p2 = fma(q.d[r] - x, p1, -q.e2[r] * p0);
+        sg = __builtin_amdgcn_alignbit(sg, (unsigned)__double2hiint(p2), 31);  // sg << 1 | sign
         p0 = p1;
         p1 = p2;
     };
-    int i = 1;
-    for (; i + 3 < J; i += 4) {  // four steps per trip: the eight loads go out together
-        const double d0 = ds[i], d1 = ds[i + 1], d2 = ds[i + 2], d3 = ds[i + 3];
-        const double f0 = e2s[i - 1], f1 = e2s[i], f2 = e2s[i + 1], f3 = e2s[i + 2];
-        step(d0, f0);
-        step(d1, f1);
-        step(d2, f2);
-        step(d3, f3);
-        const double mg = fmax(fabs(p0), fabs(p1));
-        const double f = mg > kUp ? kDown : (mg < kDown ? kUp : 1.0);
+    auto block = [&](const TRows& q) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) step(q, r);
+        c += __popc((sg ^ (sg >> 1)) & 0xffu);
+        const unsigned ex = (unsigned)__double2hiint(fmax(fabs(p0), fabs(p1))) & 0x7ff00000u;
+        const double f = __hiloint2double((int)(((2 * 1023u + kTop) << 20) - ex), 0);
         p0 *= f;
         p1 *= f;
+    };
+    auto tail = [&](const TRows& q, int left) {  // 0 to 7 rows
+#pragma unroll
+        for (int r = 0; r < 7; ++r)
+            if (r < left) step(q, r);
+        return c + __popc((sg ^ (sg >> 1)) & ((1u << left) - 1u));
+    };
+    TRows qa, qb;
+    rows.load(1, qa);
+    int i = 1;
+    for (; i + 15 < J; i += 16) {
+        rows.arrive();
+        rows.load(i + 8, qb);
+        rows.sent();
+        block(qa);
+        rows.arrive();
+        rows.load(i + 16, qa);
+        rows.sent();
+        block(qb);
     }
-    for (; i < J; ++i) step(ds[i], e2s[i - 1]);
-    return c;
+    if (i + 7 < J) {
+        rows.arrive();
+        rows.load(i + 8, qb);
+        rows.sent();
+        block(qa);
+        rows.arrive();
+        return tail(qb, J - i - 8);
+    }
+    rows.arrive();
+    return tail(qa, J - i);
 }
 
 // Sum over the 8 consecutive lanes of a row group (every lane gets the same
@@ -393,11 +468,11 @@ __host__ __device__ inline double* eig_handoff(double* scratch, int J) {
 
 // Bounds and scale of T (all threads of the workgroup): red[32..35] receive
 // the widened Gershgorin interval of the scaled T, the scale (a power of two
-// that brings |entries| to at most 1) and the norm bound; ds and e2 the
-// scaled diagonal and squared scaled off-diagonal.  The interval is a
-// minimum and a maximum, so the split over threads changes no bit.
+// that brings |entries| to at most 1) and the norm bound; ts the scaled T as
+// sturm_count reads it.  The interval is a minimum and a maximum, so the
+// split over threads changes no bit.
 __device__ __forceinline__ void scale_t(const double* d, const double* e, int J, double* red,
-                                        double* ds, double* e2) {
+                                        double2* ts) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double gl = DBL_MAX, gu = -DBL_MAX;
     for (int i = tid; i < J; i += kEigThreads) {
@@ -434,23 +509,23 @@ __device__ __forceinline__ void scale_t(const double* d, const double* e, int J,
     __syncthreads();
     const double sc = red[34];
     for (int i = tid; i < J; i += kEigThreads) {
-        ds[i] = d[i] * sc;
-        e2[i] = (e[i] * sc) * (e[i] * sc);
+        const double es = i > 0 ? e[i - 1] * sc : 0.0;
+        ts[i] = double2{d[i] * sc, i > 0 ? fmax(es * es, kMinE2) : 0.0};
     }
     __syncthreads();
 }
 
 // T, beta and the bounds to the hand-off area of a split solve.
 __device__ __forceinline__ void write_handoff(double* ho, int J, const double* d, const double* e,
-                                              const double* beta, const double* ds,
-                                              const double* e2, const double* red) {
+                                              const double* beta, const double2* ts,
+                                              const double* red) {
     const int tid = threadIdx.x;
     for (int i = tid; i < J; i += kEigThreads) {
         ho[i] = d[i];
         ho[J + i] = e[i];
         ho[2 * J + i] = beta[i];
-        ho[3 * J + i] = ds[i];
-        ho[4 * J + i] = e2[i];
+        ho[3 * J + 2 * i] = ts[i].x;
+        ho[3 * J + 2 * i + 1] = ts[i].y;
     }
     if (tid < 4) ho[5 * J + tid] = red[32 + tid];  // gl, gu, sc, tnorm
 }
@@ -688,12 +763,11 @@ __global__ __launch_bounds__(kEigThreads) void eig_reduce_tail(double* __restric
                                                                int J) {
     extern __shared__ double smem[];
     double* reg = smem;
-    double* d = smem + kTailRegion;
+    double2* ts = reinterpret_cast<double2*>(smem + kTailRegion);
+    double* d = smem + kTailRegion + 2 * J;
     double* e = d + J;
     double* beta = e + J;
-    double* e2 = beta + J;
-    double* ds = e2 + J;
-    double* red = ds + J;  // 64, then 8, then the vector buffers
+    double* red = beta + J;  // 64, then 8, then the vector buffers
     double* H = scratch + (size_t)J * J;
     double* ho = eig_handoff(scratch, J);
     const int kend = J - kGridTail;
@@ -704,8 +778,8 @@ __global__ __launch_bounds__(kEigThreads) void eig_reduce_tail(double* __restric
     }
     tridiag_regs<kGridTail>(H + (size_t)kend * J, kGridTail, kGridTail, kend, J, reg, red, d, e,
                             beta, H);
-    scale_t(d, e, J, red, ds, e2);
-    write_handoff(ho, J, d, e, beta, ds, e2, red);
+    scale_t(d, e, J, red, ts);
+    write_handoff(ho, J, d, e, beta, ts, red);
 }
 
 // Writes a vector held by 16 lanes (element t = 32 p + 2 l16 + h) to column j
@@ -771,17 +845,15 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool lead = !MULTI || blockIdx.x == 0;  // uniform: writes the rank rule's results
     double* reg = smem;                        // A (J <= 128) then the LU batch
-    double* sv = smem + region;
-    double* d = sv;              // J
+    double* sv = smem + region;  // region is even
+    double2* ts = reinterpret_cast<double2*>(sv);  // J: the scaled T (step 2)
+    double* d = sv + 2 * J;      // J
     double* e = d + J;           // J
-    double* e2 = e + J;          // J (scaled)
-    double* beta = e2 + J;       // J
-    double* pw = beta + J;       // J: A22 x
-    double* lam = pw + J;        // J (descending)
+    double* beta = e + J;        // J
+    double* vals = beta + J;     // J: the rank rule's terms
+    double* lam = vals + J;      // J (descending)
     double* shift = lam + J;     // J
-    double* dots = shift + J;    // J: v during step 1, scaled d during step 2
-    double* colv = dots + J;     // J: w during step 1
-    double* red = colv + J;      // 64
+    double* red = shift + J;     // 64
     int* misc = (int*)(red + 64);  // [0] = R
     double* H = a.scratch + (size_t)J * J;    // reflector k at H[k * J], length J - k - 1
     double* X = a.u;                          // column-major J x R
@@ -803,12 +875,11 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     if constexpr (PH != 3) {
     // ---- 1. Householder tridiagonalisation, A in registers ---------------
     tridiag_regs<JP>(a.s, J, J, 0, J, reg, red, d, e, beta, H);
-    double* ds = dots;  // scaled diagonal
-    scale_t(d, e, J, red, ds, e2);
+    scale_t(d, e, J, red, ts);
     sc = red[34];
     tnorm = red[35];
     if constexpr (PH == 1) {
-        write_handoff(ho, J, d, e, beta, ds, e2, red);
+        write_handoff(ho, J, d, e, beta, ts, red);
         return;
     }
 
@@ -824,14 +895,13 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
         const int gofs = (lane / tpe) * tpe;
         const uint64_t gmask = (((1ull << tpe) - 1ull) << gofs);
         (void)wave;
-        const double atol = 2.0 * DBL_EPSILON;  // T is scaled to norm <= 1
         double lo = gl, hi = gu;
         if (k < J) {
             for (int it = 0; it < 160; ++it) {
-                const double tol = fmax(atol, 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)));
+                const double tol = fmax(kSectTol, kSectTol * fmax(fabs(lo), fabs(hi)));
                 if (hi - lo <= tol) break;
                 const double h = (hi - lo) / (double)(tpe + 1);
-                const int c = sturm_count(ds, e2, J, lo + h * (double)(s + 1));
+                const int c = sturm_count(LdsRows{ts}, ts[0].x, J, lo + h * (double)(s + 1));
                 const uint64_t bal = __ballot(c > k) & gmask;
                 const int sstar = bal ? (__ffsll((long long)bal) - gofs) : tpe + 1;  // 1-based point
                 const double nlo = sstar == 1 ? lo : lo + h * (double)(sstar - 1);
@@ -866,8 +936,7 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
         const double l = raw ? lam[r] : fmax(lam[r], 0.0);
         return a.aug ? l * l : l;
     };
-    // the values of the tail sums, formed in parallel (pw is free after step 1)
-    double* vals = pw;
+    // the values of the tail sums, formed in parallel
     for (int i = tid; i < Jv; i += kEigThreads) {
         const double v = val(i);
         vals[i] = v;
@@ -1559,30 +1628,24 @@ __global__ __launch_bounds__(kEigThreads) void eig_kernel(EigArgs a, int region)
 // same Sturm counts and stopping rule as the one-launch solver, and stores
 // it, unscaled, at position J - 1 - k of the descending list.  TPE = 64 (one
 // eigenvalue per wave, six bits per round) suits a single solve, whose few
-// waves are latency-bound; a batch fills the GPU and is issue-bound, so
-// TPE = 16 (four eigenvalues per wave) does less work in all.
+// waves are latency-bound: more waves per eigenvalue (four: eight bits, 7
+// rounds instead of 9) gave J = 128 27 -> 25 us and J = 301 46 -> 57.
 template <int TPE>
 __device__ __forceinline__ void multisect_group(double* __restrict__ ho, int J, int k,
-                                                bool active, double* sm) {
-    double* ds = sm;
-    double* e2 = sm + J;
+                                                bool active) {
+    const ScalarRows ts(ho + 3 * J);
+    const double d0 = ho[3 * J];
     const int lane = threadIdx.x;
-    for (int i = lane; i < J; i += 64) {
-        ds[i] = ho[3 * J + i];
-        e2[i] = ho[4 * J + i];
-    }
-    __syncthreads();
     if (!active) return;  // the whole group (k is the same in its lanes)
     const int s = lane % TPE, gofs = lane - s;
-    const uint64_t gmask = TPE == 64 ? ~0ull : (((1ull << TPE) - 1ull) << gofs);
+    const uint64_t gmask = TPE == 64 ? ~0ull : (((1ull << (TPE & 63)) - 1ull) << gofs);
     double lo = ho[5 * J], hi = ho[5 * J + 1];
     const double sc = ho[5 * J + 2];
-    const double atol = 2.0 * DBL_EPSILON;  // T is scaled to norm <= 1
     for (int it = 0; it < 160; ++it) {
-        const double tol = fmax(atol, 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)));
+        const double tol = fmax(kSectTol, kSectTol * fmax(fabs(lo), fabs(hi)));
         if (hi - lo <= tol) break;  // lo, hi are the same in every lane of the group
         const double h = (hi - lo) / (double)(TPE + 1);
-        const int c = sturm_count(ds, e2, J, lo + h * (double)(s + 1));
+        const int c = sturm_count(ts, d0, J, lo + h * (double)(s + 1));
         const uint64_t bal = __ballot(c > k) & gmask;
         const int sstar = bal ? (__ffsll((long long)bal) - gofs) : TPE + 1;  // 1-based point
         const double nlo = sstar == 1 ? lo : lo + h * (double)(sstar - 1);
@@ -1594,25 +1657,26 @@ __device__ __forceinline__ void multisect_group(double* __restrict__ ho, int J, 
 }
 
 __global__ __launch_bounds__(64) void eig_multisect(double* __restrict__ scratch, int J) {
-    extern __shared__ double sm[];
-    multisect_group<64>(eig_handoff(scratch, J), J, blockIdx.x, true, sm);
+    multisect_group<64>(eig_handoff(scratch, J), J, (int)blockIdx.x, true);
 }
 
 // The same for a batch, four eigenvalues per workgroup: workgroup w takes
 // eigenvalues 4 q .. 4 q + 3 of problem w / nq, q = w % nq, nq = ceil(jmax / 4)
-// (groups beyond that problem's J do nothing).
+// (groups beyond that problem's J do nothing).  A large batch is issue-bound
+// and 16 points per round do less work in all: 60 problems of 96 rows 30 us
+// against 47 with a wave per eigenvalue, 24 problems 24 against 27; 12
+// problems, 23 against 19, do not carry a variant of their own.
 constexpr int kBatchTpe = 16;
 constexpr int kBatchGroups = 64 / kBatchTpe;
 
 __global__ __launch_bounds__(64) void eig_multisect_batched(const EigArgs* __restrict__ args,
                                                             int nq, int conditional) {
-    extern __shared__ double sm[];
     const int p = blockIdx.x / nq, q = blockIdx.x - p * nq;
     const int J = args[p].J;
     if (kBatchGroups * q >= J) return;  // uniform over the workgroup
     if (conditional && !(args[p].flags[0] & 4)) return;  // the redo pass: bit 4 only
     const int k = kBatchGroups * q + (int)threadIdx.x / kBatchTpe;
-    multisect_group<kBatchTpe>(eig_handoff(uni_global(args[p].scratch), J), J, k, k < J, sm);
+    multisect_group<kBatchTpe>(eig_handoff(uni_global(args[p].scratch), J), J, k, k < J);
 }
 
 // One workgroup per problem of a batch, as PH = 1, eig_multisect_batched,
@@ -1692,8 +1756,8 @@ int launch_eig_batched(const EigArgs* args_dev, int count, int jmax, int conditi
     };
     TK_TRY(jp == 96 ? launch(eig_batched<96, 1>) : launch(eig_batched<128, 1>));
     const int nq = (jmax + kBatchGroups - 1) / kBatchGroups;
-    hipLaunchKernelGGL(eig_multisect_batched, dim3(count * nq), dim3(64),
-                       (size_t)2 * jmax * sizeof(double), st, args_dev, nq, conditional);
+    hipLaunchKernelGGL(eig_multisect_batched, dim3(count * nq), dim3(64), 0, st, args_dev, nq,
+                       conditional);
     TK_HIP(hipGetLastError());
     return jp == 96 ? launch(eig_batched<96, 3>) : launch(eig_batched<128, 3>);
 }
@@ -1759,8 +1823,7 @@ static int launch_eig_jp(const EigArgs& a, int region, size_t lds, hipStream_t s
     } else {
         TK_TRY(launch_reduce_large(a, st));
     }
-    hipLaunchKernelGGL(eig_multisect, dim3(a.J), dim3(64), (size_t)2 * a.J * sizeof(double), st,
-                       a.scratch, a.J);
+    hipLaunchKernelGGL(eig_multisect, dim3(a.J), dim3(64), 0, st, a.scratch, a.J);
     TK_HIP(hipGetLastError());
     // a workgroup per batch of vectors up to the largest rank there can be
     const int jv = a.aug ? a.J / 2 : a.J;

@@ -1,0 +1,37 @@
+"""Sturm counts of the eigensolver: blocks of eight rows read one block ahead
+with a remainder of 0 to 7, from LDS (extents below 64) and from the hand-off
+of a split solve (64 and up), on spectra that make minors vanish."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1510_06689_amd import tucker
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -53
+
+
+def _spectrum(x):
+    """The computed spectrum is that of a matrix within about J u |S| of S = x x^T;
+    16 J u covers both sides."""
+    j = x.shape[0]
+    d = tucker.empty_fortran(x.shape, torch.float64, "cuda:0").copy_(torch.from_numpy(x))
+    got = tucker.sthosvd(d, 0.0, ranks=(1, 1)).eigvals[0].cpu().numpy()
+    lam = np.linalg.eigvalsh(x @ x.T)[::-1]
+    assert np.abs(got - lam).max() <= 16 * j * U * max(lam[0], 1e-300)
+
+
+@pytest.mark.parametrize("j", [*range(1, 19), 31, 32, 33, 47, 63, *range(64, 82), 127, 128, 136, 250])
+def test_remainders(j):
+    rng = np.random.default_rng(j)
+    q, _ = np.linalg.qr(rng.standard_normal((j, j)))
+    _spectrum(q * 0.9 ** np.arange(j))
+
+
+@pytest.mark.parametrize("j", [9, 17, 50, 72, 81, 128, 150])
+def test_vanishing_couplings(j):
+    _spectrum(np.diag(2.0 ** -np.arange(j, dtype=float)))       # every off-diagonal is zero
+    _spectrum(np.eye(j))                                        # one eigenvalue J times
+    rng = np.random.default_rng(j)
+    _spectrum(np.outer(rng.standard_normal(j), rng.standard_normal(j)))  # all but one are zero
+    _spectrum(rng.standard_normal((j, j)) * 10.0 ** -rng.integers(0, 12, (j, 1)))  # graded rows
