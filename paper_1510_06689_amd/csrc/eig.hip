@@ -283,73 +283,78 @@ __device__ __forceinline__ void tridiag_regs(const double* __restrict__ src, int
                                              double* d, double* e, double* beta, double* H) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // ---- 1. Householder tridiagonalisation, A in registers ---------------
-    // Thread t owns row i = t / 8 and the columns j = t % 8 + 8 q.  Per column
-    // k: the owners of row k form the reflector and publish v; (A22 v)_i is a
-    // sum over the row's 8 lanes and p = tau A22 v is published; each thread
-    // then updates its own elements.  Vectors alternate between two LDS
-    // buffers so that two barriers per column suffice; reflectors collect in
-    // LDS and go to the global scratch once at the end.
-    constexpr int NQ = JP / 8;
-    const int ri = tid >> 3, rc = tid & 7;
-    const bool rowok = ri < Jr;
-    double av[NQ];
+    // Thread t owns rows 2 (t / 16) and the next and of them the columns
+    // j = t % 16 + 16 q.  Per column k: the 16 owners of row k form the
+    // reflector and publish v; (A22 v)_i is a sum over the row's 16 lanes and
+    // p = tau A22 v is published; each thread then updates its own elements.
+    // Vectors alternate between two LDS buffers so that two barriers per
+    // column suffice; reflectors collect in LDS and go to the global scratch
+    // once at the end.
+    //
+    // What bounds a column: the chain of the reflector and the two exchanges,
+    // and every row's reading v and p from LDS.  Two rows per thread halve
+    // those reads against one row on eight lanes, and v and p fit in
+    // registers between the product and the update: J = 128 154 -> 130 us,
+    // J = 100 128 -> 107.  (A 32 x 32 grid of threads whose waves each form
+    // the reflector, for one barrier per column, was issue-bound: 280 us.)
+    constexpr int NQ = JP / 16;
+    const int rp = tid >> 4, rc = tid & 15, r0 = 2 * rp;
+    double av[2][NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        const int j = rc + 8 * q;
-        av[q] = (rowok && j < Jr) ? src[ri + (size_t)ld * j] : 0.0;
+        const int j = rc + 16 * q;
+        av[0][q] = (r0 < Jr && j < Jr) ? src[r0 + (size_t)ld * j] : 0.0;
+        av[1][q] = (r0 + 1 < Jr && j < Jr) ? src[r0 + 1 + (size_t)ld * j] : 0.0;
     }
     double* Hs = reg;
-    constexpr int NS = (JP + 63) / 64;  // per-lane slots of a wave-wide reduction
     // Every load below stays inside the reflector store (zeroed first, so
     // that entries no step writes are exact zeros: reflector k is written
     // from column k + 1 on) and four JP-long vector buffers in the
     // 1024-double area after misc (zeroed too; the global-A path alone uses
     // it otherwise).  Finished rows and columns see v = p = 0, so the
-    // register loops need no masks.  Each column reads v and p from LDS by
-    // every row, which bounds the step: from block KEEP on v, and from KEEP2
-    // on p, stay in registers between the matrix-vector product and the
-    // update (the live chunks shrink with the block index).
+    // register loops need no masks.
     static_assert(4 * JP <= kEigThreads, "vector buffers must fit the partial-sum area");
     double* vbuf = red + 64 + 8;
     for (int i = tid; i < 4 * JP; i += kEigThreads) vbuf[i] = 0.0;
     for (int i = tid; i < (Jr > 2 ? Jr - 2 : 0) * JP; i += kEigThreads) Hs[i] = 0.0;
     __syncthreads();
-    // Columns run in blocks of eight, the block index KB a compile-time
-    // constant: chunks below KB are finished for every column of the block
-    // (their v and p are zero), so each loop starts at chunk KB with no test,
-    // and only chunks KB and KB + 1 can hold the pivot column k + 1.
+    // Columns run in blocks of 16, the block index KB and the parity of k
+    // compile-time constants: chunks below KB are finished for every column of
+    // the block (their v and p are zero), so each loop starts at chunk KB with
+    // no test, and only chunks KB and KB + 1 can hold the pivot column k + 1.
     static_for<0, NQ>([&](auto kbc) {
         constexpr int KB = decltype(kbc)::value;
-        const int kend = min(8 * KB + 8, Jr - 2);
-        for (int k = 8 * KB; k < kend; ++k) {
-            double* vs = Hs + (size_t)k * JP;        // v = reflector k: v_{k+1} = 1, zero outside k < j < Jr
-            double* ps = vbuf + (2 + (k & 1)) * JP;  // p = tau A22 v, zero outside k < i < Jr
-            double* sg = red + 40 + (k & 1);         // tau of column k
-            // The row index goes through an empty asm so that the compiler
-            // cannot use ri == k to replace the uniform k by the per-lane ri
-            // inside the owner branch (that turns every column test below
+        auto column = [&](int k, auto parity) {
+            constexpr int PR = decltype(parity)::value;  // k & 1
+            double* vs = Hs + (size_t)k * JP;    // v = reflector k: v_{k+1} = 1, zero outside k < j < Jr
+            double* ps = vbuf + (2 + PR) * JP;   // p = tau A22 v, zero outside k < i < Jr
+            double* sg = red + 40 + PR;          // tau of column k
+            // The pair index goes through an empty asm so that the compiler
+            // cannot use rp == k / 2 to replace the uniform k by the per-lane
+            // row inside the owner branch (that turns every column test below
             // into a per-lane mask held across the loop).
-            int ri_k = ri;
-            asm volatile("" : "+v"(ri_k));
-            if (ri_k == k) {
+            int rp_k = rp;
+            asm volatile("" : "+v"(rp_k));
+            if (rp_k == (k >> 1)) {
                 // The owners of row k (= column k, x = its part beyond the
                 // diagonal) form the reflector alone, in the form of LAPACK's
                 // dlarfg: alpha = -sign(x_0) |x|, tau = 1 + |x_0| / |x|,
                 // v = x / (x_0 - alpha) (one reciprocal square root and one
                 // reciprocal), and publish v.
-                double sq[4] = {0.0, 0.0, 0.0, 0.0};
+                double sq[2] = {0.0, 0.0};
 #pragma unroll
                 for (int q = KB; q < NQ; ++q) {
-                    const double m = (q > KB + 1 || rc + 8 * q >= k + 2) ? av[q] : 0.0;
-                    sq[q & 3] = fma(m, m, sq[q & 3]);
+                    const double m = (q > KB + 1 || rc + 16 * q >= k + 2) ? av[PR][q] : 0.0;
+                    sq[q & 1] = fma(m, m, sq[q & 1]);
                 }
-                const double sigma = row8_sum((sq[0] + sq[1]) + (sq[2] + sq[3]));
+                const double sigma = row16_sum(sq[0] + sq[1]);
                 // a_kk and a_k,k+1 from the lanes of row k that hold them:
                 // column k lies in chunk KB, column k + 1 in KB or KB + 1
-                const int l0 = 8 * (k & 7);
-                const double akk = read_lane(av[KB], l0 + (k & 7));
-                const double x0 = read_lane(((k + 1) >> 3) == KB ? av[KB] : av[KB + 1 < NQ ? KB + 1 : KB],
-                                            l0 + ((k + 1) & 7));
+                const int l0 = 16 * ((k >> 1) & 3);
+                const double akk = read_lane(av[PR][KB], l0 + (k & 15));
+                const double x0 =
+                    read_lane(((k + 1) >> 4) == KB ? av[PR][KB] : av[PR][KB + 1 < NQ ? KB + 1 : KB],
+                              l0 + ((k + 1) & 15));
                 double tau = 0.0, alpha = x0, inv_v0 = 0.0;
                 if (sigma != 0.0) {
                     const double ss = fma(x0, x0, sigma);
@@ -362,8 +367,8 @@ __device__ __forceinline__ void tridiag_regs(const double* __restrict__ src, int
                 }
 #pragma unroll
                 for (int q = KB; q < NQ; ++q) {
-                    const int j = rc + 8 * q;
-                    const double vj = av[q] * inv_v0;  // av is 0 beyond Jr
+                    const int j = rc + 16 * q;
+                    const double vj = av[PR][q] * inv_v0;  // av is 0 beyond Jr
                     vs[j] = q > KB + 1 ? vj : (j == k + 1 ? 1.0 : (j > k + 1 ? vj : 0.0));
                 }
                 if (rc == 0) {
@@ -378,70 +383,65 @@ __device__ __forceinline__ void tridiag_regs(const double* __restrict__ src, int
             // A wave whose 8 rows are all <= k has nothing to form or update (uniform).
             const bool wact = 8 * wave + 7 > k;
             double part = 0.0;
-            constexpr int KEEP = 2, KEEP2 = 4;
             double vq[NQ];
             if (wact) {  // formed before tau is tested, so that v's loads do not wait for it
-                double pr[4] = {0.0, 0.0, 0.0, 0.0};
+                double s0[2] = {0.0, 0.0}, s1[2] = {0.0, 0.0};
 #pragma unroll
                 for (int q = KB; q < NQ; ++q) {
-                    vq[q] = vs[rc + 8 * q];
-                    pr[q & 3] = fma(av[q], vq[q], pr[q & 3]);
+                    vq[q] = vs[rc + 16 * q];
+                    s0[q & 1] = fma(av[0][q], vq[q], s0[q & 1]);
+                    s1[q & 1] = fma(av[1][q], vq[q], s1[q & 1]);
                 }
-                part = row8_sum((pr[0] + pr[1]) + (pr[2] + pr[3]));  // (A22 v)_i
+                // (A22 v)_i of the first row to lanes 0-7, of the second to 8-15
+                const double a0 = s0[0] + s0[1], a1 = s1[0] + s1[1];
+                const bool hi = rc >= 8;
+                part = row8_sum((hi ? a1 : a0) + dpp_move<0x140, 0xf, false>(hi ? a0 : a1));
             }
-            if (tau == 0.0) continue;  // uniform: the reflector is the identity
-            if (rc == 0 && ri < JP) ps[ri] = (wact && ri > k && rowok) ? tau * part : 0.0;
+            if (tau == 0.0) return;  // uniform: the reflector is the identity
+            const int rw = r0 + (rc >> 3);
+            if ((rc & 7) == 0 && rw < JP) ps[rw] = (wact && rw > k && rw < Jr) ? tau * part : 0.0;
             __syncthreads();
-            if (!wact) continue;  // uniform over the wave; it still meets every barrier
+            if (!wact) return;  // uniform over the wave; it still meets every barrier
             // A22 -= v w^T + w v^T with w = p - (tau/2)(p.v) v, two fused
             // multiply-adds per element; entries outside the trailing block
-            // see v = w = 0.  Every lane forms p.v with the same bits (from
-            // KEEP2 on as a sum over its row's 8 lanes, all rows holding the
-            // same values).  The update rounds a_ij and a_ji differently, so
-            // A is symmetric up to rounding; only each row's own elements are
-            // ever read, so the reduction is that of a matrix within rounding
-            // of the exact iterate.
-            double pq[NQ];
-            double half;
-            if constexpr (KB >= KEEP2) {
-                double pr2[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int q = KB; q < NQ; ++q) {
-                    pq[q] = ps[rc + 8 * q];
-                    pr2[q & 3] = fma(pq[q], vq[q], pr2[q & 3]);
-                }
-                half = 0.5 * tau * row8_sum((pr2[0] + pr2[1]) + (pr2[2] + pr2[3]));
-            } else {
-                double pv = 0.0;
-#pragma unroll
-                for (int r = 0; r < NS; ++r) {
-                    const int j = lane + 64 * r;
-                    if (j < JP) pv = fma(ps[j], vs[j], pv);
-                }
-                half = 0.5 * tau * wave_sum(pv);
-            }
-            const int ric = ri < JP ? ri : 0;
-            const double vi = vs[ric], wi = fma(-half, vi, ps[ric]);
+            // see v = w = 0.  Every row's lanes form p.v from the same values
+            // with the same bits.  The update rounds a_ij and a_ji
+            // differently, so A is symmetric up to rounding; only each row's
+            // own elements are ever read, so the reduction is that of a matrix
+            // within rounding of the exact iterate.
+            const int rr = r0 < JP ? r0 : 0;
+            const double v0 = vs[rr], v1 = vs[rr + 1], p0 = ps[rr], p1 = ps[rr + 1];
+            double pq[NQ], pv[2] = {0.0, 0.0};
 #pragma unroll
             for (int q = KB; q < NQ; ++q) {
-                double vj;
-                if constexpr (KB >= KEEP) vj = vq[q];
-                else vj = vs[rc + 8 * q];
-                double pj;
-                if constexpr (KB >= KEEP2) pj = pq[q];
-                else pj = ps[rc + 8 * q];
-                const double wj = fma(-half, vj, pj);
-                av[q] = fma(-wi, vj, fma(-vi, wj, av[q]));
+                pq[q] = ps[rc + 16 * q];
+                pv[q & 1] = fma(pq[q], vq[q], pv[q & 1]);
             }
+            const double half = 0.5 * tau * row16_sum(pv[0] + pv[1]);
+            const double w0 = fma(-half, v0, p0), w1 = fma(-half, v1, p1);
+#pragma unroll
+            for (int q = KB; q < NQ; ++q) {
+                const double wj = fma(-half, vq[q], pq[q]);
+                av[0][q] = fma(-w0, vq[q], fma(-v0, wj, av[0][q]));
+                av[1][q] = fma(-w1, vq[q], fma(-v1, wj, av[1][q]));
+            }
+        };
+        const int kend = min(16 * KB + 16, Jr - 2);
+        for (int k = 16 * KB; k < kend; k += 2) {
+            column(k, std::integral_constant<int, 0>{});
+            if (k + 1 < kend) column(k + 1, std::integral_constant<int, 1>{});
         }
     });
     // the trailing 2 x 2 block (or 1 x 1)
-    if (ri >= Jr - 2 && rowok) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int ri = r0 + h;
+        if (ri < Jr - 2 || ri >= Jr) continue;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const int j = rc + 8 * q;
-            if (j == ri) d[koff + ri] = av[q];
-            if (ri == Jr - 2 && j == Jr - 1) e[koff + Jr - 2] = av[q];
+            const int j = rc + 16 * q;
+            if (j == ri) d[koff + ri] = av[h][q];
+            if (ri == Jr - 2 && j == Jr - 1) e[koff + Jr - 2] = av[h][q];
         }
     }
     if (tid == 0) {

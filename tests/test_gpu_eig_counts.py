@@ -35,3 +35,23 @@ def test_vanishing_couplings(j):
     rng = np.random.default_rng(j)
     _spectrum(np.outer(rng.standard_normal(j), rng.standard_normal(j)))  # all but one are zero
     _spectrum(rng.standard_normal((j, j)) * 10.0 ** -rng.integers(0, 12, (j, 1)))  # graded rows
+
+
+@pytest.mark.parametrize("j,r", [(15, 15), (16, 5), (17, 17), (33, 20), (48, 11), (95, 9), (96, 30), (97, 3), (113, 40), (128, 12)])
+def test_reduction_blocks(j, r):
+    """Two rows per thread, columns in blocks of 16: vectors at the blocks' edges,
+    with a column that needs no reflector among them.  |S u - u lambda| is bounded by
+    the backward error of the solve, 16 J u |S| on either side as above."""
+    rng = np.random.default_rng(7 * j + r)
+    q, _ = np.linalg.qr(rng.standard_normal((j, j)))
+    x = q * 0.9 ** np.arange(j)
+    x[:, : j // 3] *= np.arange(j)[:, None] % 3 != 1
+    s = x @ x.T
+    d = tucker.empty_fortran(x.shape, torch.float64, "cuda:0").copy_(torch.from_numpy(x))
+    t = tucker.sthosvd(d, 0.0, ranks=(r, j))
+    got, u = t.eigvals[0].cpu().numpy(), t.factors[0].cpu().numpy()
+    lam = np.linalg.eigvalsh(s)[::-1]
+    tol = 16 * j * U * lam[0]
+    assert np.abs(got - lam).max() <= tol
+    assert np.abs(u.T @ u - np.eye(r)).max() <= 16 * j * U
+    assert np.abs(s @ u - u * got[:r]).max() <= 4 * tol
