@@ -6,13 +6,14 @@
 //      derives the reflector from the pivot row, forms p = tau A22 v, then
 //      applies the rank-2 update A22 -= v w^T + w v^T.  For J <= 128 the
 //      matrix lives in one workgroup's registers; otherwise the first
-//      J - 128 columns are reduced by 64 single-wave workgroups that hold it
-//      together (eig_reduce_grid), and one workgroup finishes the last
-//      128 x 128 block; the reflectors go to global scratch;
+//      J - 192 columns, if any, are reduced by 64 single-wave workgroups that
+//      hold it together (eig_reduce_grid), one workgroup brings the last 192
+//      to 128 (eig_reduce_mid) and one finishes those (eig_reduce_tail); the
+//      reflectors go to global scratch;
 //   2. all eigenvalues of T by multisection: groups of threads per
 //      eigenvalue evaluate Sturm counts with the three-term determinant
-//      recurrence of T scaled by a power of two (exact), rescaled by 2^+-300
-//      every four steps; a ballot picks the sub-interval;
+//      recurrence of T scaled by a power of two (exact), rescaled (exactly)
+//      every eight rows; a ballot picks the sub-interval;
 //   3. rank rule R = min R >= 1 with sum_{r>R} max(lambda_r,0) <= eps^2 nu / N
 //      (tail sums accumulated smallest first), or a fixed rank;
 //   4. the R leading eigenvectors of T by inverse iteration (tridiagonal LU
@@ -532,16 +533,16 @@ __device__ __forceinline__ void write_handoff(double* ho, int J, const double* d
 
 // ---------------------------------------------- reduction of extents > 128
 //
-// The first J - 128 columns of a matrix too large for one workgroup's
+// The first J - 192 columns of a matrix too large for one workgroup's
 // registers.  One workgroup streaming A22 from L2 took 12 us per column at
 // J = 256 (one CU's load path and three barriers); here kGridWaves single-wave
 // workgroups hold all of A in registers for the whole reduction (wave w owns
 // rows w + 64 q, lane t of it the columns t + 64 s), so a column costs one
 // exchange between them and no barrier: about 3 us, most of it the trip of a
-// value from one XCD to another.  Whole reductions, this part and the last
-// 128 columns: J = 187 0.80 -> 0.32 ms, J = 250 1.72 -> 0.56, J = 301
-// 3.69 -> 0.78.  All waves on one XCD was slower (J = 301: 0.85 against
-// 0.64 ms for this part).  In column k
+// value from one XCD to another.  Whole reductions, with these columns and the
+// last 192 in one workgroup: J = 187 0.80 -> 0.25 ms, J = 250 1.72 -> 0.48,
+// J = 301 3.69 -> 0.68.  All waves on one XCD was slower (J - 128 columns of
+// J = 301: 0.85 against 0.64 ms).  In column k
 //   - every wave holds the pivot row k and forms the reflector (v, tau) from
 //     it redundantly, with the same bits;
 //   - it publishes p_i = tau (A v)_i for its rows i > k, and the owner of row
@@ -559,7 +560,8 @@ __device__ __forceinline__ void write_handoff(double* ho, int J, const double* d
 // same: after kGridSpins reads a wave takes NaN for what is missing, waits
 // no more, and sets flag bit 4, which fails the call.
 constexpr int kGridWaves = 64;
-constexpr int kGridTail = 128;  // columns left to the register reduction
+constexpr int kMidRows = 192;   // rows left to one workgroup,
+constexpr int kGridTail = 128;  // of them those left to the register reduction
 constexpr unsigned long long kNotYet = 0xFFF7A5C39B1E64D2ull;
 constexpr int kGridSpins = 1 << 21;
 
@@ -601,11 +603,11 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
                                                       int* __restrict__ flags) {
     const int lane = threadIdx.x;
     const int w = blockIdx.x;
-    double* P = scratch;                        // [J - 128][J] products
+    double* P = scratch;                        // [J - 192][J] products
     double* H = scratch + (size_t)J * J;        // reflectors
-    double* Rw = scratch + (size_t)2 * J * J;   // [J - 128][J] pivot rows
+    double* Rw = scratch + (size_t)2 * J * J;   // [J - 192][J] pivot rows
     double* ho = eig_handoff(scratch, J);
-    const int kend = J - kGridTail;
+    const int kend = J - kMidRows;
     double a[NS][NS];  // a[q][s]: row w + 64 q, column lane + 64 s
     double r[NS];      // pivot row, 0 before column k
 #pragma unroll
@@ -735,19 +737,163 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
             }
         }
     }
-    // the trailing 128 x 128 block, in the room of the reflectors still to come
+    // the trailing 192 x 192 block, in the room of the reflectors still to come
     double* T = H + (size_t)kend * J;
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
         const int i = w + 64 * q - kend;
-        if (i >= 0 && i < kGridTail) {
+        if (i >= 0 && i < kMidRows) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int j = lane + 64 * s - kend;
-                if (j >= 0 && j < kGridTail) T[(size_t)i * kGridTail + j] = a[q][s];
+                if (j >= 0 && j < kMidRows) T[(size_t)i * kMidRows + j] = a[q][s];
             }
         }
     }
+}
+
+// The columns that bring a symmetric block of n = 129 .. 192 rows to 128, in
+// one workgroup's registers; element (i, j) is src[i ld + j].  Thread t owns
+// the rows t / 16 + 64 h, h < 3, of the block set at the lower end of 192
+// positions, and of them the columns t % 16 + 16 q: the rows that finish here
+// are those of h = 0, and the 128 that remain need no test.  Columns run as in
+// the register reduction of at most 128 rows (tridiag_regs), two exchanges
+// through LDS each; its store for the reflectors has room for these 64
+// columns, not for all of 192.  What bounds a column is the same chain and
+// the rows' reads of v and p from LDS: 2.0 us each at 192 rows, where one
+// exchange between workgroups on different XCDs takes 3.2.  Whole reductions,
+// with these 64 columns in place of the grid's: J = 187 295 -> 245 us,
+// J = 250 540 -> 475, J = 301 755 -> 680.
+constexpr int kMidLds = (64 * kMidRows + 2 * kMidRows + 3 * 64 + 2) * (int)sizeof(double);
+
+__global__ __launch_bounds__(kEigThreads) void eig_reduce_mid(const double* src, int ld, int n,
+                                                              int J, double* scratch) {
+    extern __shared__ double smem[];
+    constexpr int NQ = kMidRows / 16;
+    double* Hs = smem;                      // reflector k at row k, zero up to k
+    double* pb = smem + 64 * kMidRows;      // p, two buffers
+    double* dv = pb + 2 * kMidRows;         // d, e, beta
+    double* sgb = dv + 3 * 64;              // tau, two buffers
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = tid >> 4, rc = tid & 15;
+    const int off = kMidRows - n;           // position of the block's first row
+    const int koff = J - n;
+    double av[3][NQ];
+#pragma unroll
+    for (int h = 0; h < 3; ++h)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int i = g + 64 * h - off, j = rc + 16 * q - off;
+            av[h][q] = i >= 0 && j >= 0 ? src[(size_t)i * ld + j] : 0.0;
+        }
+    for (int i = tid; i < 64 * kMidRows; i += kEigThreads) Hs[i] = 0.0;
+    __syncthreads();
+    static_for<0, 4>([&](auto kbc) {
+        constexpr int KB = decltype(kbc)::value;  // chunks below KB are finished
+        for (int k = max(16 * KB, off); k < 16 * KB + 16; ++k) {
+            double* vs = Hs + k * kMidRows;
+            double* ps = pb + (k & 1) * kMidRows;
+            double* sg = sgb + (k & 1);
+            int g_k = g;  // as in tridiag_regs: k stays uniform inside the branch
+            asm volatile("" : "+v"(g_k));
+            if (g_k == k) {
+                double sq[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int q = KB; q < NQ; ++q) {
+                    const double m = (q > KB + 1 || rc + 16 * q >= k + 2) ? av[0][q] : 0.0;
+                    sq[q & 3] = fma(m, m, sq[q & 3]);
+                }
+                const double sigma = row16_sum((sq[0] + sq[1]) + (sq[2] + sq[3]));
+                const int l0 = 16 * (k & 3);
+                const double akk = read_lane(av[0][KB], l0 + (k & 15));
+                const double x0 = read_lane(((k + 1) >> 4) == KB ? av[0][KB] : av[0][KB + 1],
+                                            l0 + ((k + 1) & 15));
+                double tau = 0.0, alpha = x0, inv_v0 = 0.0;
+                if (sigma != 0.0) {
+                    const double ss = fma(x0, x0, sigma);
+                    const double r = rsq(ss);  // 1 / |x|
+                    const double mu = ss * r;
+                    const double sgn = x0 < 0.0 ? -1.0 : 1.0;
+                    alpha = -sgn * mu;
+                    tau = fma(fabs(x0), r, 1.0);
+                    inv_v0 = sgn * recip(fabs(x0) + mu);
+                }
+#pragma unroll
+                for (int q = KB; q < NQ; ++q) {
+                    const int j = rc + 16 * q;
+                    const double vj = av[0][q] * inv_v0;
+                    vs[j] = q > KB + 1 ? vj : (j == k + 1 ? 1.0 : (j > k + 1 ? vj : 0.0));
+                }
+                if (rc == 0) {
+                    *sg = tau;
+                    dv[k] = akk;
+                    dv[64 + k] = alpha;
+                    dv[128 + k] = tau;
+                }
+            }
+            __syncthreads();
+            const double tau = *sg;
+            const bool top = 4 * wave + 3 > k;  // uniform: a row of h = 0 is left
+            double vq[NQ], s0 = 0.0, s1[2] = {0.0, 0.0}, s2[2] = {0.0, 0.0};
+#pragma unroll
+            for (int q = KB; q < NQ; ++q) {
+                vq[q] = vs[rc + 16 * q];
+                s1[q & 1] = fma(av[1][q], vq[q], s1[q & 1]);
+                s2[q & 1] = fma(av[2][q], vq[q], s2[q & 1]);
+            }
+            if (top) {
+                double t[2] = {0.0, 0.0};
+#pragma unroll
+                for (int q = KB; q < NQ; ++q) t[q & 1] = fma(av[0][q], vq[q], t[q & 1]);
+                s0 = row16_sum(t[0] + t[1]);
+            }
+            // the sum of row 64 + g to lanes 0-7, of row 128 + g to 8-15
+            const double a1 = s1[0] + s1[1], a2 = s2[0] + s2[1];
+            const bool hi = rc >= 8;
+            const double part = row8_sum((hi ? a2 : a1) + dpp_move<0x140, 0xf, false>(hi ? a1 : a2));
+            if (tau == 0.0) continue;  // uniform: the reflector is the identity
+            if ((rc & 7) == 0) ps[g + 64 + 64 * (rc >> 3)] = tau * part;
+            if (rc == 0) ps[g] = g > k ? tau * s0 : 0.0;
+            __syncthreads();
+            double pv = 0.0;
+#pragma unroll
+            for (int h = 0; h < 3; ++h) pv = fma(ps[lane + 64 * h], vs[lane + 64 * h], pv);
+            const double half = 0.5 * tau * wave_sum(pv);
+            double vi[3], wi[3];
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {
+                vi[h] = vs[g + 64 * h];
+                wi[h] = fma(-half, vi[h], ps[g + 64 * h]);
+            }
+#pragma unroll
+            for (int q = KB; q < NQ; ++q) {
+                const double wj = fma(-half, vq[q], ps[rc + 16 * q]);
+                if (top) av[0][q] = fma(-wi[0], vq[q], fma(-vi[0], wj, av[0][q]));
+                av[1][q] = fma(-wi[1], vq[q], fma(-vi[1], wj, av[1][q]));
+                av[2][q] = fma(-wi[2], vq[q], fma(-vi[2], wj, av[2][q]));
+            }
+        }
+    });
+    __syncthreads();
+    double* H = scratch + (size_t)J * J;
+    double* ho = eig_handoff(scratch, J);
+    for (int k = off + wave; k < 64; k += kEigWaves)
+        for (int i = lane; i < kMidRows - k - 1; i += 64)
+            H[(size_t)(koff + k - off) * J + i] = Hs[k * kMidRows + k + 1 + i];
+    if (tid >= off && tid < 64) {
+        const int k = koff + tid - off;
+        ho[k] = dv[tid];
+        ho[J + k] = dv[64 + tid];
+        ho[2 * J + k] = dv[128 + tid];
+    }
+    // the trailing 128 x 128 block, in the room of the reflectors still to come
+    double* T = H + (size_t)(J - kGridTail) * J;
+#pragma unroll
+    for (int h = 1; h < 3; ++h)
+#pragma unroll
+        for (int q = 4; q < NQ; ++q)
+            T[(size_t)(g + 64 * (h - 1)) * kGridTail + rc + 16 * (q - 4)] = av[h][q];
 }
 
 // Extents above 128: the register reduction of the trailing block, then the
@@ -1792,21 +1938,31 @@ static int launch_reduce_grid(const EigArgs& a, hipStream_t st) {
 
 // Steps 1 of an extent above 128, leaving T in the hand-off area.
 static int launch_reduce_large(const EigArgs& a, hipStream_t st) {
-    const int n = (a.J - kGridTail) * a.J;  // slots of each kind
     const size_t jj = (size_t)a.J * a.J;
-    hipLaunchKernelGGL(eig_slots_fill, dim3((n + 255) / 256), dim3(256), 0, st,
-                       (unsigned long long*)a.scratch, (unsigned long long*)(a.scratch + 2 * jj),
-                       n);
-    TK_HIP(hipGetLastError());
-    switch ((a.J + 63) / 64) {
-        case 3: TK_TRY(launch_reduce_grid<3>(a, st)); break;
-        case 4: TK_TRY(launch_reduce_grid<4>(a, st)); break;
-        case 5: TK_TRY(launch_reduce_grid<5>(a, st)); break;
-        case 6: TK_TRY(launch_reduce_grid<6>(a, st)); break;
-        case 7: TK_TRY(launch_reduce_grid<7>(a, st)); break;
-        case 8: TK_TRY(launch_reduce_grid<8>(a, st)); break;
-        default: return fail(TK_ERR_UNSUPPORTED, "eigensolver: extent %d", a.J);
+    const double* src = a.s;
+    int n = a.J;
+    if (a.J > kMidRows) {
+        const int slots = (a.J - kMidRows) * a.J;  // of each kind
+        hipLaunchKernelGGL(eig_slots_fill, dim3((slots + 255) / 256), dim3(256), 0, st,
+                           (unsigned long long*)a.scratch,
+                           (unsigned long long*)(a.scratch + 2 * jj), slots);
+        TK_HIP(hipGetLastError());
+        switch ((a.J + 63) / 64) {
+            case 4: TK_TRY(launch_reduce_grid<4>(a, st)); break;
+            case 5: TK_TRY(launch_reduce_grid<5>(a, st)); break;
+            case 6: TK_TRY(launch_reduce_grid<6>(a, st)); break;
+            case 7: TK_TRY(launch_reduce_grid<7>(a, st)); break;
+            case 8: TK_TRY(launch_reduce_grid<8>(a, st)); break;
+            default: return fail(TK_ERR_UNSUPPORTED, "eigensolver: extent %d", a.J);
+        }
+        src = a.scratch + jj + (size_t)(a.J - kMidRows) * a.J;
+        n = kMidRows;
     }
+    TK_HIP(hipFuncSetAttribute((const void*)eig_reduce_mid,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, kMidLds));
+    hipLaunchKernelGGL(eig_reduce_mid, dim3(1), dim3(kEigThreads), kMidLds, st, src, n, n, a.J,
+                       a.scratch);
+    TK_HIP(hipGetLastError());
     const size_t lds = eig_tail_lds_bytes(a.J);
     TK_HIP(hipFuncSetAttribute((const void*)eig_reduce_tail,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));

@@ -37,10 +37,10 @@ def test_vanishing_couplings(j):
     _spectrum(rng.standard_normal((j, j)) * 10.0 ** -rng.integers(0, 12, (j, 1)))  # graded rows
 
 
-@pytest.mark.parametrize("j,r", [(15, 15), (16, 5), (17, 17), (33, 20), (48, 11), (95, 9), (96, 30), (97, 3), (113, 40), (128, 12)])
+@pytest.mark.parametrize("j,r", [(144, 9), (145, 7), (159, 4), (161, 5), (176, 6), (177, 8), (208, 3), (15, 15), (16, 5), (17, 17), (33, 20), (48, 11), (95, 9), (96, 30), (97, 3), (113, 40), (128, 12)])
 def test_reduction_blocks(j, r):
-    """Two rows per thread, columns in blocks of 16: vectors at the blocks' edges,
-    with a column that needs no reflector among them.  |S u - u lambda| is bounded by
+    """Two rows per thread (above 128 rows three), columns in blocks of 16: vectors at the
+    blocks' edges, with rows of zeros among them.  |S u - u lambda| is bounded by
     the backward error of the solve, 16 J u |S| on either side as above."""
     rng = np.random.default_rng(7 * j + r)
     q, _ = np.linalg.qr(rng.standard_normal((j, j)))
