@@ -224,6 +224,12 @@ struct QrGeom {
 // columns later, after every wave has passed the next barrier (and so
 // finished this step).  R row k, column c is read and written only by the
 // wave owning c.
+// Products and updates are formed for every slot from KB on, also for columns
+// that are finished or padding: their w is zero, as only live columns take one
+// from the sum.  A test per slot set each slot's four fma's apart in a block
+// of their own, one dependent chain after another (a tile of 256 x 128: 170 ->
+// 142 us).  Forming the next reflector ahead of the rest of its wave's update
+// on top of this was slower (150 us).
 template <int JC, int KB>
 __device__ __forceinline__ void absorb_block(double (&a)[QrGeom<JC>::RPL][QrGeom<JC>::CPW],
                                              int J, int wave, int lane, double* Rs,
@@ -260,8 +266,7 @@ __device__ __forceinline__ void absorb_block(double (&a)[QrGeom<JC>::RPL][QrGeom
 #pragma unroll
         for (int q = OFFS; q < CPW; ++q) {
             double s = 0.0;
-            const int c = wave + kQrWaves * q;
-            if (q >= KB && (q > KB || wave > kk) && c < J) {  // uniform
+            if (q >= KB) {
 #pragma unroll
                 for (int p = 0; p < RPL; ++p) s = fma(v[p], a[p][q], s);
             }
@@ -290,11 +295,8 @@ __device__ __forceinline__ void absorb_block(double (&a)[QrGeom<JC>::RPL][QrGeom
         }
 #pragma unroll
         for (int q = KB; q < CPW; ++q) {
-            const int c = wave + kQrWaves * q;
-            if ((q > KB || wave > kk) && c < J) {  // uniform
 #pragma unroll
-                for (int p = 0; p < RPL; ++p) a[p][q] = fma(-v[p], wq[q], a[p][q]);
-            }
+            for (int p = 0; p < RPL; ++p) a[p][q] = fma(-v[p], wq[q], a[p][q]);
         }
     }
 }
