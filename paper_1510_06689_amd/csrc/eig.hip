@@ -17,7 +17,8 @@
 //   3. rank rule R = min R >= 1 with sum_{r>R} max(lambda_r,0) <= eps^2 nu / N
 //      (tail sums accumulated smallest first), or a fixed rank;
 //   4. the R leading eigenvectors of T by inverse iteration (tridiagonal LU
-//      with partial pivoting kept in LDS, reciprocal pivots, two sweeps),
+//      with partial pivoting from both ends to the middle, kept in LDS,
+//      reciprocal pivots, two iterations),
 //      in batches that fit in LDS, then modified Gram-Schmidt (twice) inside
 //      eigenvalue clusters by one wave;
 //   5. back-transformation X <- Q X, 16 lanes per eigenvector with the
@@ -43,9 +44,14 @@ constexpr int kInvIters = 2;
 constexpr int kLuArrays = 6;  // u0 (reciprocal), u1, u2, multiplier, pivot flag, x
 constexpr int kSweepRows = 4;  // rows per block of the inverse-iteration sweeps
 
-// Rows of the inverse-iteration arrays: J padded to whole sweep blocks.
+// Rows of the inverse-iteration arrays: half of J (two threads carry a
+// vector), padded to whole sweep blocks, and the doubles of one of the two
+// records: kLuArrays per row and one more.
 __host__ __device__ constexpr int eig_sweep_rows(int J) {
-    return (J + kSweepRows - 1) / kSweepRows * kSweepRows;
+    return ((J + 1) / 2 + kSweepRows - 1) / kSweepRows * kSweepRows;
+}
+__host__ __device__ constexpr int eig_record_doubles(int J) {
+    return kLuArrays * eig_sweep_rows(J) + 1;
 }
 
 // Moves a double across lanes with one DPP pattern (applied to both 32-bit
@@ -134,9 +140,8 @@ static size_t eig_region_doubles(int J) {
     const size_t lds_doubles = 160 * 1024 / sizeof(double);
     size_t cap = lds_doubles - eig_small_doubles(J) - 128;
     if (cap > 16384) cap = 16384;                 // J <= 128 also holds A here (J*J <= 16384)
-    // room for every vector in one batch: a record of kLuArrays values per
-    // padded row plus one, and two scale factors, per vector
-    const size_t want = ((size_t)kLuArrays * eig_sweep_rows(J) + 3) * J;
+    // room for every vector in one batch: two records and two scale factors
+    const size_t want = ((size_t)2 * eig_record_doubles(J) + 2) * J;
     return (want < cap ? want : cap) & ~size_t(1);  // even: what follows holds 16-byte pairs
 }
 
@@ -1178,7 +1183,16 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
 
 
     // ---- 4. inverse iteration, batches of vectors held in LDS -----------
-    // One thread per vector runs the recurrences on a record of its own in
+    // Two threads, neighbouring lanes, carry a vector: they eliminate T - sg I
+    // from its two ends (the rows are taken in even number: behind an odd J
+    // comes one that is coupled to nothing) and meet in the middle, where one
+    // row each with the two middle unknowns is left, a 2 x 2 system with
+    // pivoting; both sweeps then run towards and away from there.  What bounds
+    // this is the chain from row to row of one wave, about 400 cycles in the
+    // factorisation and 230 per iteration; each thread walks half the rows
+    // (the launch at J = 128, 16 vectors 114 -> 92 us, J = 100 66 -> 53,
+    // J = 250, 100 vectors 102 -> 64).
+    // Each thread works on a record of its own in
     // LDS: row i holds (x, reciprocal pivot, u1, u2, multiplier, pivot flag)
     // at rec[kLuArrays i ..], so every access is the thread's base plus an
     // immediate offset; the record's last double is x of row Jb (zero), and
@@ -1192,22 +1206,24 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     // its result, with the same two roundings as an in-place pass.
     const double tiny = DBL_EPSILON * tnorm + DBL_MIN;
     const int Jb = eig_sweep_rows(J);
-    const int recd = kLuArrays * Jb + 1;  // doubles per record
-    const int batch = (int)((size_t)region / ((size_t)recd + 2));
+    const int half = (J + 1) / 2;  // rows of either thread, counted from its end
+    const int recd = eig_record_doubles(J);
+    const int batch = (int)((size_t)region / ((size_t)2 * recd + 2));
     constexpr int oX = 0, oRP = 1, oU1 = 2, oU2 = 3, oLM = 4, oPV = 5;
     const int jfirst = MULTI ? (int)blockIdx.x * batch : 0;
     const int jlast = MULTI ? min(R, jfirst + batch) : R;
     if (MULTI && jfirst >= R) return;  // uniform over the workgroup
     for (int j0 = jfirst; j0 < jlast; j0 += batch) {
         const int nb = min(batch, R - j0);
-        double* SC1 = reg + (size_t)recd * nb;  // nb: pending scale factors of x
+        double* SC1 = reg + (size_t)2 * recd * nb;  // nb: pending scale factors of x
         double* SC2 = SC1 + nb;
         __syncthreads();  // the region is free (A or the previous batch)
         // deterministic start vectors, zero in the padding rows and row Jb
-        for (int idx = tid; idx < (Jb + 1) * nb; idx += kEigThreads) {
-            const int jj = idx / (Jb + 1), i = idx - jj * (Jb + 1);
-            reg[(size_t)jj * recd + kLuArrays * i + oX] =
-                i < J ? hash_unit((uint32_t)(j0 + jj), (uint32_t)i) : 0.0;
+        for (int idx = tid; idx < (Jb + 1) * 2 * nb; idx += kEigThreads) {
+            const int rr = idx / (Jb + 1), i = idx - rr * (Jb + 1);
+            const int t = rr & 1 ? 2 * half - 1 - i : i;  // row of T
+            reg[(size_t)rr * recd + kLuArrays * i + oX] =
+                i < half && t < J ? hash_unit((uint32_t)(j0 + (rr >> 1)), (uint32_t)t) : 0.0;
         }
         __syncthreads();
         // meanwhile the last wave hands the call's scalars to the host, which
@@ -1221,11 +1237,17 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                 __hip_atomic_store((uint64_t*)(a.host + kHostScalars), a.host_seq,
                                    __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        if (tid < nb) {
+        if (tid < 2 * nb) {
             constexpr int IB = kSweepRows;
             constexpr int W = kLuArrays;
-            const int jj = tid, j = j0 + tid;
-            double* rec = reg + (size_t)jj * recd;
+            const int jj = tid >> 1, j = j0 + jj;
+            const bool low = tid & 1;  // from the last row up
+            double* rec = reg + (size_t)tid * recd;
+            // row i of this thread's half and its coupling to row i + 1
+            const int st = low ? -1 : 1;
+            const double* dp = low ? d + (2 * half - 1) : d;
+            const double* ep = low ? e + (2 * half - 2) : e;
+            auto partner = [](double v) { return dpp_move<0xb1, 0xf, false>(v); };
             // Row i0 of the record.  The offset goes through an empty asm so
             // that each block forms one address and reaches its rows by
             // immediate offsets (the compiler otherwise keeps one address per
@@ -1238,21 +1260,21 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
             const double sg = shift[j];
             const double rtiny = recip(tiny);  // recip(-tiny) = -recip(tiny) exactly
             // LU factorisation of T - sg I with partial pivoting
-            double ai = d[0] - sg, bi = (J > 1) ? e[0] : 0.0;
-            for (int i0 = 0; i0 + 1 < J; i0 += IB) {
+            double ai = low && (J & 1) ? 1.0 : dp[low && (J & 1) ? -1 : 0] - sg;
+            double bi = ep[0];  // e[J - 1] is 0
+            for (int i0 = 0; i0 + 1 < half; i0 += IB) {
                 double cb[IB], anb[IB], bnb[IB];
 #pragma unroll
                 for (int u = 0; u < IB; ++u) {
-                    const int i = min(i0 + u, J - 2);
-                    cb[u] = e[i];
-                    anb[u] = d[i + 1] - sg;
-                    const double en = e[i + 1];
-                    bnb[u] = (i + 2 < J) ? en : 0.0;
+                    const int i = min(i0 + u, half - 2);
+                    cb[u] = ep[st * i];
+                    anb[u] = dp[st * (i + 1)] - sg;
+                    bnb[u] = ep[st * (i + 1)];
                 }
                 double* rr = row(i0);
 #pragma unroll
                 for (int u = 0; u < IB; ++u) {
-                    if (i0 + u + 1 < J) {  // uniform
+                    if (i0 + u + 1 < half) {  // uniform
                         // Without interchange (|a_i| >= |c_i|) the pivot is a_i,
                         // raised to +-tiny if smaller; with it the pivot is c_i
                         // (|c_i| > |a_i|), the multiplier uses c_i itself and only
@@ -1278,21 +1300,33 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                     }
                 }
             }
-            if (fabs(ai) < tiny) ai = (ai < 0.0 ? -tiny : tiny);
-            // The last row has no superdiagonal terms and no multiplier; the
+            // The last row's unknown comes from the middle system; it and the
             // padding rows are all zero (their pivot reciprocal included).
-            for (int i = J - 1; i < Jb; ++i) {
-                rec[W * i + oRP] = i == J - 1 ? recip(ai) : 0.0;
+            for (int i = half - 1; i < Jb; ++i) {
+                rec[W * i + oRP] = 0.0;
                 rec[W * i + oU1] = 0.0;
                 rec[W * i + oU2] = 0.0;
                 rec[W * i + oLM] = 0.0;
                 rec[W * i + oPV] = 0.0;
             }
+            // Middle system a1 y + b1 z = r1, b2 y + a2 z = r2 (1: the thread
+            // from the first row, y its last unknown): the pivot row has p, pc,
+            // the other one multiplier ml and pivot q.  Both threads form the
+            // same bits.
+            const double ao = partner(ai), bo = partner(bi);
+            const double a1 = low ? ao : ai, b1 = low ? bo : bi;
+            const double a2 = low ? ai : ao, b2 = low ? bi : bo;
+            const bool swp = fabs(b2) > fabs(a1);
+            auto raised = [&](double v) { return fabs(v) < tiny ? (v < 0.0 ? -tiny : tiny) : v; };
+            const double pc = swp ? a2 : b1;
+            const double rpm = recip(raised(swp ? b2 : a1));
+            const double ml = (swp ? a1 : b2) * rpm;
+            const double rqm = recip(raised(fma(-ml, pc, swp ? b1 : a2)));
             double f1 = 1.0, f2 = 1.0;  // x = (stored x f1) f2
             // Both sweeps alternate two register sets: the next block's loads
             // are issued before this block's arithmetic and stores.  Rows past
-            // J (all in the last block) carry zeros: the forward sweep maps a
-            // zero row to zero, the backward one forces them.
+            // the half (all in the last block) carry zeros: the forward sweep
+            // maps a zero row to zero, the backward one forces them.
             for (int it = 0; it < kInvIters; ++it) {
                 // forward: row interchanges and multipliers, running value in xc
                 double xA[IB], pA[IB], lA[IB], xB[IB], pB[IB], lB[IB];
@@ -1346,17 +1380,27 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                         rb[u] = rr[W * u + oRP];
                     }
                 };
-                double x1 = 0.0, x2 = 0.0, amax = 0.0;
+                const double rl = rec[W * (half - 1) + oX], ro = partner(rl);
+                const double r1 = low ? ro : rl, r2 = low ? rl : ro;
+                const double rp1 = swp ? r2 : r1, rs1 = swp ? r1 : r2;
+                const double zm = fma(-ml, rp1, rs1) * rqm;
+                const double ym = fma(-pc, zm, rp1) * rpm;
+                double x1 = low ? zm : ym, x2 = low ? ym : zm, amax = fabs(x1);
                 auto bstep = [&](auto top, int i0, const double (&xb)[IB], const double (&u1b)[IB],
                                  const double (&u2b)[IB], const double (&rb)[IB]) {
                     double ob[IB];
 #pragma unroll
                     for (int u = IB - 1; u >= 0; --u) {
+                        if constexpr (decltype(top)::value) {
+                            if (i0 + u >= half - 1) {  // uniform
+                                ob[u] = i0 + u == half - 1 ? x1 : 0.0;
+                                continue;
+                            }
+                        }
                         double v = xb[u];
                         v = fma(-u1b[u], x1, v);
                         v = fma(-u2b[u], x2, v);
                         v *= rb[u];
-                        if constexpr (decltype(top)::value) v = i0 + u < J ? v : 0.0;
                         ob[u] = v;
                         x2 = x1;
                         x1 = v;
@@ -1378,24 +1422,30 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
                     bstep(std::false_type{}, i0 - IB, xB, u1B, u2B, rB);
                     if (i0 == IB) break;
                 }
+                amax = fmax(amax, partner(amax));
                 double nrm2 = 0.0;
                 const double scl = amax > 0.0 ? 1.0 / amax : 1.0;
 #pragma unroll 8
-                for (int i = 0; i < J; ++i) {
+                for (int i = 0; i < half; ++i) {
                     const double v = rec[W * i + oX] * scl;
                     nrm2 += v * v;
                 }
+                nrm2 += partner(nrm2);
                 f1 = scl;
                 f2 = nrm2 > 0.0 ? 1.0 / sqrt(nrm2) : 0.0;
             }
-            SC1[jj] = f1;
-            SC2[jj] = f2;
+            if (!low) {
+                SC1[jj] = f1;
+                SC2[jj] = f2;
+            }
         }
         __syncthreads();
         for (int idx = tid; idx < J * nb; idx += kEigThreads) {
             const int jj = idx / J, i = idx - jj * J;
+            const bool low = i >= half;
+            const double* x = reg + (size_t)(2 * jj + low) * recd + oX;
             X[(size_t)(j0 + jj) * J + i] =
-                (reg[(size_t)jj * recd + kLuArrays * i + oX] * SC1[jj]) * SC2[jj];
+                (x[kLuArrays * (low ? 2 * half - 1 - i : i)] * SC1[jj]) * SC2[jj];
         }
     }
     if constexpr (MULTI)
@@ -1915,7 +1965,7 @@ constexpr int kSplitEig = 64;
 // Vectors of inverse iteration that one workgroup's LDS region holds.
 static int eig_batch(int J) {
     const size_t region = eig_region_doubles_jp(J, eig_jp(J));
-    return (int)(region / ((size_t)kLuArrays * eig_sweep_rows(J) + 3));
+    return (int)(region / ((size_t)2 * eig_record_doubles(J) + 2));
 }
 
 template <int JP, int PH>

@@ -55,3 +55,36 @@ def test_reduction_blocks(j, r):
     assert np.abs(got - lam).max() <= tol
     assert np.abs(u.T @ u - np.eye(r)).max() <= 16 * j * U
     assert np.abs(s @ u - u * got[:r]).max() <= 4 * tol
+
+
+@pytest.mark.parametrize("j", [1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 40, 63, 64, 65, 90, 127, 128, 129, 170])
+@pytest.mark.parametrize("kind", ["decay", "middle", "twice"])
+def test_vectors_from_two_ends(j, kind):
+    """Inverse iteration eliminates from both ends and meets in the middle: every
+    parity and padding of a half; an entry alone in the middle; the same block on
+    either side of it, so that every eigenvalue comes twice.  Residual and
+    orthogonality bounds as above."""
+    rng = np.random.default_rng(31 * j + len(kind))
+    if kind == "twice" and j >= 4:
+        m = j // 2
+        q, _ = np.linalg.qr(rng.standard_normal((m, m)))
+        b = q * 0.8 ** np.arange(m)
+        x = np.zeros((j, j))
+        x[:m, :m] = b
+        x[j - m:, j - m:] = b
+    else:
+        q, _ = np.linalg.qr(rng.standard_normal((j, j)))
+        x = q * 0.9 ** np.arange(j)
+        if kind == "middle":
+            x[j // 2] = 0.0
+            x[j // 2, j // 2] = 1.5
+    r = min(j, 14)
+    s = x @ x.T
+    d = tucker.empty_fortran(x.shape, torch.float64, "cuda:0").copy_(torch.from_numpy(x))
+    t = tucker.sthosvd(d, 0.0, ranks=(r, j))
+    got, u = t.eigvals[0].cpu().numpy(), t.factors[0].cpu().numpy()
+    lam = np.linalg.eigvalsh(s)[::-1]
+    tol = 16 * j * U * lam[0]
+    assert np.abs(got - lam).max() <= tol
+    assert np.abs(u.T @ u - np.eye(r)).max() <= 16 * j * U
+    assert np.abs(s @ u - u * got[:r]).max() <= 4 * tol
