@@ -53,7 +53,7 @@ struct GramSched {
     static constexpr int KT = NB <= 2 ? 128 : NB <= 4 ? 64 : 32;
     static constexpr int NP = NB * (NB + 1) / 2;
     static constexpr int NPW = KS == 1 ? (NP + W - 1) / W : NP;
-    static constexpr int kLds = 2 * 16 * NB * (KT + 1) + 64;  // doubles: two tile buffers, trash
+    static constexpr int kLds = 2 * kTileBuf<NB, KT>;  // doubles
     static constexpr int kPerCu = NB <= 8 ? 2 : 1;
 };
 
@@ -80,7 +80,7 @@ __device__ __forceinline__ void gram_f64_walk(const T* __restrict__ y, const Til
                                               int64_t t0, int64_t t1, double* __restrict__ out,
                                               double* lds) {
     typedef GramSched<NB> S;
-    constexpr int P = S::KT + 1, NPW = S::NPW, NP = S::NP, BUF = 16 * NB * P;
+    constexpr int P = S::KT + 1, NPW = S::NPW, NP = S::NP, BUF = kTileBuf<NB, S::KT>;
     constexpr int KQ = S::KT / 8 / S::KS;  // steps of eight columns, of a wave per tile
     constexpr bool ALL = S::KS > 1;        // a wave has all pairs
     const int tid = threadIdx.x, lane = tid & 63;
@@ -92,7 +92,7 @@ __device__ __forceinline__ void gram_f64_walk(const T* __restrict__ y, const Til
     constexpr int PER = decltype(st)::kPer;
     if (t0 < t1) {
         // tile t0 to the first buffer, tile t0 + 1 on its way to the registers
-        st.begin(y, tm, t0, t1, 2 * BUF);
+        st.begin(y, tm, t0, t1);
 #pragma unroll
         for (int q = 0; q < PER; ++q) st.load(q);
         st.advance();
@@ -250,7 +250,7 @@ constexpr int kWideThreads = 512, kWideWaves = kWideThreads / 64;
 constexpr int kWideNpw = 14, kWidePairs = kWideWaves * kWideNpw, kWideKt = 16;
 // NB: the block count rounded up to a multiple of four (it sizes the stage).
 template <int NB>
-constexpr int kWideBuf = 16 * NB * (kWideKt + 1);
+constexpr int kWideBuf = kTileBuf<NB, kWideKt>;
 
 template <typename T, int NB, bool PACKED>
 __device__ __forceinline__ void gram_wide_body(const T* __restrict__ y, const TileMap& tm, int nb,
@@ -271,7 +271,7 @@ __device__ __forceinline__ void gram_wide_body(const T* __restrict__ y, const Ti
     }
     TileStage<T, NB, kWideKt, kWideThreads, PACKED> st;
     if (t0 < t1) {
-        st.begin(y, tm, t0, t1, 2 * kWideBuf<NB>);
+        st.begin(y, tm, t0, t1);
 #pragma unroll
         for (int q = 0; q < st.kPer; ++q) st.load(q);
         st.advance();
@@ -363,7 +363,7 @@ static int launch_gram_f64_t(const T* y, const ModeView& v, const GramPlan& pl, 
         return fail(TK_ERR_UNSUPPORTED, "mode extent %d exceeds %d", v.J, TK_MAX_MODE_DIM);
     auto launch = [&](auto nbc) -> int {
         constexpr int NB = decltype(nbc)::value;
-        const size_t lds = (2 * kWideBuf<NB> + 64) * sizeof(double);
+        const size_t lds = 2 * kWideBuf<NB> * sizeof(double);
         auto fn = gram_partial_wide<T, NB>;
         TK_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)lds));

@@ -100,16 +100,21 @@ struct ColumnTile {
 //   such, so lanes stay dense and lines are read once whatever L and J are.
 //   strided: thread t reads column t % KT of row t / KT (+ passes).
 // LDS: rows at or past J and a packed tile's padding columns are never
-// written and must be zeroed first; behind the buffers, 64 doubles at `trash`
-// take the stores of lanes without an element.
+// written and must be zeroed first.  A buffer (kTileBuf) ends with 64 doubles
+// that take the stores of lanes without an element: they belong to the buffer,
+// so every offset is valid from the start of either one.
+template <int NB, int KT>
+constexpr int kTileBuf = 16 * NB * (KT + 1) + 64;
+
 template <typename T, int NB, int KT, int THREADS, bool PACKED>
 struct TileStage {
     static_assert(16 * NB * KT % THREADS == 0 && THREADS % KT == 0, "tile over threads");
     static constexpr int kPer = 16 * NB * KT / THREADS;
     static constexpr int P = KT + 1;
     static constexpr int RS = THREADS / KT;  // rows per pass
+    static constexpr int kTrash = kTileBuf<NB, KT> - 64;
     T v[kPer];
-    int at[PACKED ? kPer : 1];  // LDS offset of each element; strided: of the first row
+    int at[PACKED ? kPer : 1];  // offset of each element in a buffer; strided: of the first row
     int64_t row0;               // strided: offset of this thread's first row
     int tid, kk, J;
     int64_t L;
@@ -122,7 +127,7 @@ struct TileStage {
 
     // Tiles t0 .. t1 - 1 (t0 < t1), the last one repeated when asked for more.
     __device__ __forceinline__ void begin(const T* __restrict__ y, const TileMap& tm, int64_t t0,
-                                          int64_t t1, int trash) {
+                                          int64_t t1) {
         tid = threadIdx.x;
         J = tm.J;
         L = tm.L;
@@ -143,7 +148,7 @@ struct TileStage {
 #pragma unroll
             for (int q = 0; q < kPer; ++q) {
                 const int in = i * P + bb * Li + l;
-                at[q] = tid + q * THREADS < total ? in : trash + (tid & 63);
+                at[q] = tid + q * THREADS < total ? in : kTrash + (tid & 63);
                 l += l1;
                 i += i1;
                 bb += b1;
@@ -196,11 +201,11 @@ struct TileStage {
             v[q] = (p + (int64_t)pass_row(q) * L)[row0 + min(kk, n - 1)];
     }
 
-    __device__ __forceinline__ void store(double* lds, int q) const {
+    __device__ __forceinline__ void store(double* buf, int q) const {
         if constexpr (PACKED)
-            lds[at[q]] = tid + q * THREADS < nreg ? (double)v[q] : 0.0;
+            buf[at[q]] = tid + q * THREADS < nreg ? (double)v[q] : 0.0;
         else
-            lds[at[0] + pass_row(q) * P] = kk < nreg ? (double)v[q] : 0.0;
+            buf[at[0] + pass_row(q) * P] = kk < nreg ? (double)v[q] : 0.0;
     }
 };
 

@@ -26,7 +26,7 @@ constexpr int kRegThreads = 512;
 template <int JC>
 constexpr int kRegKt = JC <= 128 ? 64 : 32;
 template <int JC>
-constexpr size_t kRegLds = (size_t)(2 * JC * (kRegKt<JC> + 1) + 64) * sizeof(double);
+constexpr size_t kRegLds = (size_t)2 * kTileBuf<JC / 16, kRegKt<JC>> * sizeof(double);
 
 // ZT: form Z^T blocks, so that the lanes of a quarter-wave write consecutive
 // output rows r (columns of the tile fewer than 16 apart in memory, L < 16);
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kRegThreads, 2) void ttm_reg_f64(
     const T* __restrict__ y, TileMap tm, const double* __restrict__ m, int64_t ldm, int K,
     int transpose, T* __restrict__ z) {
     extern __shared__ double lds[];
-    constexpr int KT = kRegKt<JC>, P = KT + 1, BUF = JC * P;
+    constexpr int KT = kRegKt<JC>, P = KT + 1, BUF = kTileBuf<JC / 16, KT>;
     constexpr int WC = 8 / WR, CB = KT / 16;
     constexpr int NC = CB / WC;  // column blocks per wave
     static_assert(CB % WC == 0, "column blocks over waves");
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kRegThreads, 2) void ttm_reg_f64(
     for (int e = tid; e < 2 * BUF; e += kRegThreads) lds[e] = 0.0;
     TileStage<T, JC / 16, KT, kRegThreads, PACKED> st;
     constexpr int PER = decltype(st)::kPer;
-    st.begin(y, tm, t0, t1, 2 * BUF);
+    st.begin(y, tm, t0, t1);
 #pragma unroll
     for (int q = 0; q < PER; ++q)
         st.load(q);
