@@ -40,6 +40,10 @@
  *
  * Threading.  Calls are re-entrant as long as concurrent calls use distinct
  * workspaces and outputs.
+ * The eigensolver spreads part of an extent above 192 over 64 waves that wait
+ * for one another.  Where other streams, other processes or a stream's CU mask
+ * keep some of them from running for about 10 ms, one workgroup does that part
+ * instead: the same result, bit for bit, up to about 30 ms later.
  */
 #ifndef TUCKER_H
 #define TUCKER_H

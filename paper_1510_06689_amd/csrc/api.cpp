@@ -595,12 +595,9 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
                 fp64_modes |= 1u << n;
             }
             const bool finite = std::isfinite(sc[0]);
-            if (!finite || (flags & (2 | 16))) TK_HIP(hipStreamSynchronize(st));
+            if (!finite || (flags & 2)) TK_HIP(hipStreamSynchronize(st));
             if (!finite)
                 return fail(TK_ERR_NONFINITE, "sthosvd_compress: input holds Inf or NaN");
-            if (flags & 16)
-                return fail(TK_ERR_EIG_NO_CONVERGENCE, "sthosvd_compress: mode %d: the "
-                            "eigensolver's workgroups did not all run", n);
             if (flags & 2)
                 return fail(TK_ERR_CAPACITY, "sthosvd_compress: rank of mode %d exceeds max_ranks",
                             n);
@@ -641,9 +638,6 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
     const int flags = flags_of(sc);
     if (!std::isfinite(nu_host))
         return fail(TK_ERR_NONFINITE, "sthosvd_compress: input holds Inf or NaN");
-    if (flags & 16)
-        return fail(TK_ERR_EIG_NO_CONVERGENCE, "sthosvd_compress: the eigensolver's workgroups "
-                    "did not all run");
     if (flags & 2) return fail(TK_ERR_CAPACITY, "sthosvd_compress: a rank exceeds max_ranks");
     for (int n = 0; n < N; ++n) {
         out->ranks[n] = cur[n];

@@ -558,17 +558,22 @@ __device__ __forceinline__ void write_handoff(double* ho, int J, const double* d
 // kNotYet beforehand, so a value carries its own arrival: no flags, no order
 // between stores, and 64-bit relaxed agent-scope atomics are all it needs.
 // A result equal to the fill pattern (a NaN payload) is published as the
-// default NaN.  64 waves of one SIMD lane each wait for one another, so all
-// have to be resident: they take at most half a SIMD's registers and no LDS,
-// 2048 of them fit the GPU, and a queue has at most one partly dispatched
-// kernel, which leaves room for 32 queues.  Each wait is bounded all the
-// same: after kGridSpins reads a wave takes NaN for what is missing, waits
-// no more, and sets flag bit 4, which fails the call.
+// default NaN.  The 64 waves wait for one another, so all have to be
+// resident.  They take at most half a SIMD's registers and no LDS, 2048 of
+// them fit the GPU, and a queue has at most one partly dispatched kernel; but
+// work of other streams or processes can keep some from starting for as long
+// as it runs, and a stream's CU mask for good.  So a wave that has found
+// something missing kGridPolls times in all sets flag bit 4 and waits no more,
+// the others follow, and the workgroup that takes over the last 192 rows first
+// does these columns itself (reduce_alone): the same operations in the same
+// order, so the same bits.  A poll takes 0.17 us, the limit 11 ms; the columns
+// by one workgroup take 1.4 ms at J = 250, 3.2 at J = 301, 17 at J = 512.
 constexpr int kGridWaves = 64;
 constexpr int kMidRows = 192;   // rows left to one workgroup,
 constexpr int kGridTail = 128;  // of them those left to the register reduction
 constexpr unsigned long long kNotYet = 0xFFF7A5C39B1E64D2ull;
-constexpr int kGridSpins = 1 << 21;
+constexpr int kGridPolls = 1 << 16;
+constexpr int kGaveUp = 16;  // flag bit 4
 
 __device__ __forceinline__ void slot_put(double* p, double v) {
     unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -601,11 +606,29 @@ __device__ __forceinline__ double grid_entry(const double (&x)[NS], int g) {
     return r;
 }
 
+// Reflector of x = (x_0, rest) with |rest|^2 = sigma: alpha = -sign(x_0) |x|,
+// v = (1, rest inv_v0), tau; the identity (tau = 0) for sigma = 0.
+__device__ __forceinline__ void grid_reflector(double x0, double sigma, double& tau,
+                                               double& alpha, double& inv_v0) {
+    tau = 0.0;
+    alpha = x0;
+    inv_v0 = 0.0;
+    if (sigma != 0.0) {
+        const double ss = fma(x0, x0, sigma);
+        const double rs = rsq(ss);
+        const double mu = ss * rs;
+        const double sgn = x0 < 0.0 ? -1.0 : 1.0;
+        alpha = -sgn * mu;
+        tau = fma(fabs(x0), rs, 1.0);
+        inv_v0 = sgn * recip(fabs(x0) + mu);
+    }
+}
+
 // NS = ceil(J / 64) slots per lane; rows and columns at or past J are zero.
 template <int NS>
 __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__ S, int J,
                                                       double* __restrict__ scratch,
-                                                      int* __restrict__ flags) {
+                                                      int* flags, int polls) {
     const int lane = threadIdx.x;
     const int w = blockIdx.x;
     double* P = scratch;                        // [J - 192][J] products
@@ -624,7 +647,6 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
         }
 #pragma unroll
     for (int s = 0; s < NS; ++s) r[s] = lane + 64 * s < J ? S[lane + 64 * s] : 0.0;
-    int spins = kGridSpins;
     if (w == 0 && lane == 0) ho[0] = r[0];  // d_0
 
     for (int k = 0; k < kend; ++k) {
@@ -649,17 +671,8 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
             const double m = lane + 64 * s >= k + 2 ? r[s] : 0.0;
             sq = fma(m, m, sq);
         }
-        const double sigma = wave_sum(sq);
-        double tau = 0.0, alpha = x0, inv_v0 = 0.0;
-        if (sigma != 0.0) {
-            const double ss = fma(x0, x0, sigma);
-            const double rs = rsq(ss);
-            const double mu = ss * rs;
-            const double sgn = x0 < 0.0 ? -1.0 : 1.0;
-            alpha = -sgn * mu;
-            tau = fma(fabs(x0), rs, 1.0);
-            inv_v0 = sgn * recip(fabs(x0) + mu);
-        }
+        double tau, alpha, inv_v0;
+        grid_reflector(x0, wave_sum(sq), tau, alpha, inv_v0);
         double v[NS];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
@@ -712,9 +725,14 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
                 rn[s] = __longlong_as_double((long long)br[s]);
             }
             if (!__any(wait)) break;
-            if (--spins <= 0) {  // not reached unless a wave was never run: kNotYet is a NaN
-                spins = 0;
-                if (lane == 0) atomicOr(flags, 16);
+            // another wave has given up (looked at now and then), or this one does:
+            // what is missing is a NaN (kNotYet), and what follows is not used
+            if ((--polls & 63) == 0 &&
+                (uni(__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) & kGaveUp))
+                polls = 0;
+            if (polls <= 0) {
+                polls = 0;
+                if (lane == 0) atomicOr(flags, kGaveUp);
                 break;
             }
         }
@@ -757,6 +775,79 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
     }
 }
 
+// What eig_reduce_grid does, by one workgroup, with A in the scratch (where the
+// products' slots were).  Every wave sum has the lanes, and every element the
+// operations, of there.  lds: 3 TK_MAX_MODE_DIM doubles.
+__device__ __forceinline__ void reduce_alone(const double* __restrict__ S, int J, double* scratch,
+                                             double* lds) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double* A = scratch;
+    double* H = scratch + (size_t)J * J;
+    double* ho = eig_handoff(scratch, J);
+    double* rs = lds;                        // pivot row, 0 before column k
+    double* vs = lds + TK_MAX_MODE_DIM;      // v
+    double* ps = lds + 2 * TK_MAX_MODE_DIM;  // p
+    const int kend = J - kMidRows;
+    for (int i = tid; i < J * J; i += kEigThreads) A[i] = S[i];
+    for (int j = tid; j < J; j += kEigThreads) rs[j] = S[j];
+    if (tid == 0) ho[0] = S[0];
+    __syncthreads();
+    for (int k = 0; k < kend; ++k) {
+        const int s0 = (k + 1) & ~63;  // columns before it see v = w = 0
+        double sq = 0.0;
+        for (int j = s0 + lane; j < J; j += 64) {
+            const double m = j >= k + 2 ? rs[j] : 0.0;
+            sq = fma(m, m, sq);
+        }
+        double tau, alpha, inv_v0;
+        grid_reflector(rs[k + 1], wave_sum(sq), tau, alpha, inv_v0);
+        if (wave == 0) {
+            for (int j = s0 + lane; j < J; j += 64) {
+                const double v = j >= k + 2 ? rs[j] * inv_v0 : (j == k + 1 ? 1.0 : 0.0);
+                vs[j] = v;
+                if (j > k) H[(size_t)k * J + (j - k - 1)] = v;
+                if (j <= k) ps[j] = 0.0;
+            }
+            if (lane == 0) {
+                ho[J + k] = alpha;
+                ho[2 * J + k] = tau;
+            }
+        }
+        __syncthreads();
+        for (int i = wave; i < J; i += kEigWaves) {
+            if (i <= k) continue;  // uniform
+            double t = 0.0;
+            for (int j = s0 + lane; j < J; j += 64) t = fma(A[(size_t)i * J + j], vs[j], t);
+            t = tau * wave_sum(t);
+            if (lane == 0) ps[i] = t;
+        }
+        __syncthreads();
+        double pv = 0.0;
+        for (int j = s0 + lane; j < J; j += 64) pv = fma(ps[j], vs[j], pv);
+        const double half = 0.5 * tau * wave_sum(pv);
+        const double w1 = fma(-half, vs[k + 1], ps[k + 1]);
+        for (int i = wave; i < J; i += kEigWaves) {
+            if (i <= k) continue;  // uniform
+            const double vi = vs[i], wi = fma(-half, vi, ps[i]);
+            for (int j = s0 + lane; j < J; j += 64) {
+                const double a = A[(size_t)i * J + j], v = vs[j], w = fma(-half, v, ps[j]);
+                if (i == k + 1) {  // the next pivot row, from the row as it was
+                    const double x = fma(-w1, v, a - w);
+                    rs[j] = j > k ? x : 0.0;
+                    if (j == k + 1) ho[k + 1] = x;
+                }
+                A[(size_t)i * J + j] = fma(-wi, v, fma(-vi, w, a));
+            }
+        }
+        __syncthreads();
+    }
+    double* T = H + (size_t)kend * J;
+    for (int i = kend + wave; i < J; i += kEigWaves)
+        for (int j = kend + lane; j < J; j += 64)
+            T[(size_t)(i - kend) * kMidRows + (j - kend)] = A[(size_t)i * J + j];
+}
+
 // The columns that bring a symmetric block of n = 129 .. 192 rows to 128, in
 // one workgroup's registers; element (i, j) is src[i ld + j].  Thread t owns
 // the rows t / 16 + 64 h, h < 3, of the block set at the lower end of 192
@@ -771,9 +862,16 @@ __global__ __launch_bounds__(64) void eig_reduce_grid(const double* __restrict__
 // J = 250 540 -> 475, J = 301 755 -> 680.
 constexpr int kMidLds = (64 * kMidRows + 2 * kMidRows + 3 * 64 + 2) * (int)sizeof(double);
 
+// S, flags: eig_reduce_grid's, where it ran before; NULL elsewhere.
 __global__ __launch_bounds__(kEigThreads) void eig_reduce_mid(const double* src, int ld, int n,
-                                                              int J, double* scratch) {
+                                                              int J, double* scratch,
+                                                              const double* S, int* flags) {
     extern __shared__ double smem[];
+    if (flags && (*flags & kGaveUp)) {  // uniform
+        reduce_alone(S, J, scratch, smem);
+        __syncthreads();
+        if (threadIdx.x == 0) *flags &= ~kGaveUp;
+    }
     constexpr int NQ = kMidRows / 16;
     double* Hs = smem;                      // reflector k at row k, zero up to k
     double* pb = smem + 64 * kMidRows;      // p, two buffers
@@ -1979,44 +2077,47 @@ static int launch_eig_phase(const EigArgs& a, int region, size_t lds, int wgs, h
 }
 
 template <int NS>
-static int launch_reduce_grid(const EigArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(eig_reduce_grid<NS>, dim3(kGridWaves), dim3(64), 0, st, a.s, a.J, a.scratch,
-                       a.flags);
+static int launch_reduce_grid(const double* s, int J, double* scratch, int* flags, int polls,
+                              hipStream_t st) {
+    hipLaunchKernelGGL(eig_reduce_grid<NS>, dim3(kGridWaves), dim3(64), 0, st, s, J, scratch, flags,
+                       polls);
     TK_HIP(hipGetLastError());
     return TK_OK;
 }
 
-// Steps 1 of an extent above 128, leaving T in the hand-off area.
-static int launch_reduce_large(const EigArgs& a, hipStream_t st) {
-    const size_t jj = (size_t)a.J * a.J;
-    const double* src = a.s;
-    int n = a.J;
-    if (a.J > kMidRows) {
-        const int slots = (a.J - kMidRows) * a.J;  // of each kind
+int launch_eig_reduce(const double* s, int J, double* scratch, int* flags, int polls,
+                      hipStream_t st) {
+    if (J <= 128 || J > TK_MAX_MODE_DIM)
+        return fail(TK_ERR_UNSUPPORTED, "eigensolver's reduction: extent %d", J);
+    const size_t jj = (size_t)J * J;
+    const double* src = s;
+    int n = J;
+    if (J > kMidRows) {
+        const int slots = (J - kMidRows) * J;  // of each kind
         hipLaunchKernelGGL(eig_slots_fill, dim3((slots + 255) / 256), dim3(256), 0, st,
-                           (unsigned long long*)a.scratch,
-                           (unsigned long long*)(a.scratch + 2 * jj), slots);
+                           (unsigned long long*)scratch, (unsigned long long*)(scratch + 2 * jj),
+                           slots);
         TK_HIP(hipGetLastError());
-        switch ((a.J + 63) / 64) {
-            case 4: TK_TRY(launch_reduce_grid<4>(a, st)); break;
-            case 5: TK_TRY(launch_reduce_grid<5>(a, st)); break;
-            case 6: TK_TRY(launch_reduce_grid<6>(a, st)); break;
-            case 7: TK_TRY(launch_reduce_grid<7>(a, st)); break;
-            case 8: TK_TRY(launch_reduce_grid<8>(a, st)); break;
-            default: return fail(TK_ERR_UNSUPPORTED, "eigensolver: extent %d", a.J);
+        switch ((J + 63) / 64) {
+            case 4: TK_TRY(launch_reduce_grid<4>(s, J, scratch, flags, polls, st)); break;
+            case 5: TK_TRY(launch_reduce_grid<5>(s, J, scratch, flags, polls, st)); break;
+            case 6: TK_TRY(launch_reduce_grid<6>(s, J, scratch, flags, polls, st)); break;
+            case 7: TK_TRY(launch_reduce_grid<7>(s, J, scratch, flags, polls, st)); break;
+            default: TK_TRY(launch_reduce_grid<8>(s, J, scratch, flags, polls, st)); break;
         }
-        src = a.scratch + jj + (size_t)(a.J - kMidRows) * a.J;
+        src = scratch + jj + (size_t)(J - kMidRows) * J;
         n = kMidRows;
     }
+    const bool grid = J > kMidRows;
     TK_HIP(hipFuncSetAttribute((const void*)eig_reduce_mid,
                                hipFuncAttributeMaxDynamicSharedMemorySize, kMidLds));
-    hipLaunchKernelGGL(eig_reduce_mid, dim3(1), dim3(kEigThreads), kMidLds, st, src, n, n, a.J,
-                       a.scratch);
+    hipLaunchKernelGGL(eig_reduce_mid, dim3(1), dim3(kEigThreads), kMidLds, st, src, n, n, J,
+                       scratch, grid ? s : nullptr, grid ? flags : nullptr);
     TK_HIP(hipGetLastError());
-    const size_t lds = eig_tail_lds_bytes(a.J);
+    const size_t lds = eig_tail_lds_bytes(J);
     TK_HIP(hipFuncSetAttribute((const void*)eig_reduce_tail,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(eig_reduce_tail, dim3(1), dim3(kEigThreads), lds, st, a.scratch, a.J);
+    hipLaunchKernelGGL(eig_reduce_tail, dim3(1), dim3(kEigThreads), lds, st, scratch, J);
     TK_HIP(hipGetLastError());
     return TK_OK;
 }
@@ -2027,7 +2128,7 @@ static int launch_eig_jp(const EigArgs& a, int region, size_t lds, hipStream_t s
         if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, 1, st);
         TK_TRY((launch_eig_phase<JP, 1>(a, region, lds, 1, st)));
     } else {
-        TK_TRY(launch_reduce_large(a, st));
+        TK_TRY(launch_eig_reduce(a.s, a.J, a.scratch, a.flags, kGridPolls, st));
     }
     hipLaunchKernelGGL(eig_multisect, dim3(a.J), dim3(64), 0, st, a.scratch, a.J);
     TK_HIP(hipGetLastError());

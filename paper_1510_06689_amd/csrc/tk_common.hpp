@@ -198,8 +198,8 @@ struct EigArgs {
     int64_t* rank_out;     // device
     double* disc_out;      // device
     int* flags;            // device status flags (bit 0: no convergence, bit 1: capacity,
-                           // bit 2: rank within the guard margin, bit 4: the reduction
-                           // of an extent above 128 gave up waiting)
+                           // bit 2: rank within the guard margin, bit 4: set and cleared
+                           // inside the reduction of an extent above 192)
     double* scratch;       // eig_scratch_doubles(J)
     // Guard of a rank found from a split-bf16 Gram.  With Y the unfolding
     // (K columns), Y~ its split representation and D = Y - Y~, the Gram
@@ -285,6 +285,13 @@ inline bool mixed_takes_fp64_gram(const ModeView& v) {
 }
 size_t eig_scratch_doubles(int J);
 int launch_eig(const EigArgs& a, hipStream_t st);
+// Its reduction to tridiagonal form for extents above 128, which leaves T, the
+// reflectors' factors and T's bounds in the hand-off area of the scratch.
+// polls: how often a wave of the part spread over workgroups (extents above
+// 192) may find another one's results missing before one workgroup does that
+// part, with the same result.
+int launch_eig_reduce(const double* s, int J, double* scratch, int* flags, int polls,
+                      hipStream_t st);
 // Completes the vectors of a launch_eig once its rank R is known on the host
 // (Gram-Schmidt and back-transformation over several workgroups); nothing to
 // do where launch_eig ended them itself.  Must follow it on the same stream.
