@@ -69,14 +69,25 @@ using namespace tk;
 
 // Pinned host memory of a calling thread, allocated once and kept for the
 // thread's lifetime (512 bytes): kHostScalars doubles and the sequence number
-// that the eigensolver writes behind them (EigArgs::host).  A call is
-// synchronous, so a thread has one publication under way at most; one that a
-// failed call did not see arrive is waited for before the block is used again.
+// that the eigensolver writes behind them (EigArgs::host).  A call has one
+// publication under way at most, and none when it returns (PublicationEnd):
+// the thread's next call may use another stream on another device.
 struct HostBlock {
     double* p = nullptr;    // as the host sees it
     double* dev = nullptr;  // as the device sees it
     uint64_t seq = 0;
     bool pending = false;
+};
+
+// Ends a publication that a failing call leaves behind on its stream.
+struct PublicationEnd {
+    HostBlock* hb;
+    hipStream_t st;
+    ~PublicationEnd() {
+        if (!hb || !hb->pending) return;
+        (void)hipStreamSynchronize(st);
+        hb->pending = false;
+    }
 };
 
 static HostBlock* host_block() {  // NULL: pinned memory could not be had
@@ -102,10 +113,6 @@ static HostBlock* host_block() {  // NULL: pinned memory could not be had
 
 int tk::read_block(const double* dev, size_t n, double* host, hipStream_t st) {
     HostBlock* hb = host_block();
-    if (hb && hb->pending) {
-        TK_HIP(hipDeviceSynchronize());
-        hb->pending = false;
-    }
     double* h = hb ? hb->p : host;  // pageable memory is the fallback
     TK_HIP(hipMemcpyAsync(h, dev, n * sizeof(double), hipMemcpyDeviceToHost, st));
     TK_HIP(hipStreamSynchronize(st));
@@ -114,15 +121,13 @@ int tk::read_block(const double* dev, size_t n, double* host, hipStream_t st) {
 }
 
 // Makes the eigensolver launched with ea publish the scalar block.
-static int publish_arm(HostBlock* hb, const double* scal, EigArgs* ea) {
+static void publish_arm(HostBlock* hb, const double* scal, EigArgs* ea) {
     ea->host = nullptr;
-    if (!hb || !hb->dev) return TK_OK;
-    if (hb->pending) TK_HIP(hipDeviceSynchronize());
+    if (!hb || !hb->dev) return;
     ea->host = hb->dev;
     ea->host_scal = scal;
     ea->host_seq = ++hb->seq;
     hb->pending = true;
-    return TK_OK;
 }
 
 static bool published(const HostBlock* hb, uint64_t seq) {
@@ -147,6 +152,7 @@ static int wait_scalars(HostBlock* hb, const EigArgs& ea, const double* scal, do
         } else if (e != hipSuccess) {
             return fail(TK_ERR_HIP, "waiting for a rank: %s", hipGetErrorString(e));
         } else if (!published(hb, ea.host_seq)) {
+            hb->pending = false;
             return read_block(scal, kHostScalars, out, st);  // done without it
         }
         look = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
@@ -517,6 +523,7 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
     const int ttm_prec = opt->fixed_ranks ? opt->ttm_precision
                                           : ttm_precision_for_eps(opt->ttm_precision, eps2n);
     HostBlock* hb = host_block();
+    const PublicationEnd end{hb, st};
     EigArgs final_ea;
     double sc[kHostScalars];
     auto flags_of = [](const double* block) {
@@ -570,7 +577,7 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
         // the rank (and, after the first Gram, ||X||^2) must reach the host;
         // with fixed ranks only the last mode's scalars do, after the call
         const bool known = opt->fixed_ranks && s > 0;
-        if (!known || s + 1 == N) TK_TRY(publish_arm(hb, scal, &ea));
+        if (!known || s + 1 == N) publish_arm(hb, scal, &ea);
         if (s + 1 == N) final_ea = ea;
         TK_TRY(launch_eig(ea, st));
 
@@ -587,7 +594,7 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
                                    gram_ws, pl.gram_bytes, st));
                 ea.guard = 0.0;  // an FP64 Gram: plain rank rule
                 ea.split_stats = nullptr;
-                TK_TRY(publish_arm(hb, scal, &ea));
+                publish_arm(hb, scal, &ea);
                 if (s + 1 == N) final_ea = ea;
                 TK_TRY(launch_eig(ea, st));
                 TK_TRY(wait_scalars(hb, ea, scal, sc, st));
@@ -628,8 +635,8 @@ int sthosvd_compress(const tk_shape* x, const void* x_dev, const tk_options* opt
     }
     // the last mode's publication holds every mode's scalars
     TK_HIP(hipStreamSynchronize(st));
+    if (hb) hb->pending = false;
     if (final_ea.host && published(hb, final_ea.host_seq)) {
-        hb->pending = false;
         memcpy(sc, hb->p, sizeof sc);
     } else {
         TK_TRY(read_block(scal, kHostScalars, sc, st));
