@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstring>
 #include <mutex>
+#include <thread>
 #include <vector>
 
 #include "tk_common.hpp"
@@ -138,13 +139,16 @@ static bool published(const HostBlock* hb, uint64_t seq) {
 // rank; its vectors, and what the host enqueues next, are still to run.  (A
 // copy and a synchronisation instead cost 30 to 40 us of idle device per
 // mode: the copy's launch, the host's wake-up and the next launch's way.)
-// The stream is looked at every 2 ms, so that a failed one ends the wait.
+// Between looks the thread gives its core to whoever else is waiting for one:
+// a whole Gram may have to pass.  The stream is looked at every 2 ms, so that a
+// failed one ends the wait.
 static int wait_scalars(HostBlock* hb, const EigArgs& ea, const double* scal, double* out,
                         hipStream_t st) {
     if (!ea.host) return read_block(scal, kHostScalars, out, st);
     auto look = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
     while (!published(hb, ea.host_seq)) {
         for (int i = 0; i < 64; ++i) __builtin_ia32_pause();
+        std::this_thread::yield();
         if (std::chrono::steady_clock::now() < look) continue;
         const hipError_t e = hipStreamQuery(st);
         if (e == hipErrorNotReady) {

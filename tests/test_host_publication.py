@@ -22,6 +22,7 @@ static int __builtin_amdgcn_readfirstlane(int x) { return x; }
 
 namespace {
 std::map<hipStream_t, std::vector<std::function<void()>>> todo;
+int queries_busy, yields;  // the stream is busy for so many queries; a yield lets it run
 int eigs, ttms, fail_eig, fail_ttm;  // fail_x: the x-th launch fails after enqueueing its kernel
 
 void drain(hipStream_t st) {
@@ -45,7 +46,16 @@ EXPORT hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind
     return hipSuccess;
 }
 EXPORT hipError_t hipStreamSynchronize(hipStream_t st) { return drain(st), hipSuccess; }
-EXPORT hipError_t hipStreamQuery(hipStream_t st) { return drain(st), hipSuccess; }
+EXPORT hipError_t hipStreamQuery(hipStream_t st) {
+    if (queries_busy > 0) return --queries_busy, hipErrorNotReady;
+    return drain(st), hipSuccess;
+}
+EXPORT int sched_yield() {
+    ++yields;
+    if (queries_busy > 0)
+        for (auto& t : todo) drain(t.first);
+    return 0;
+}
 EXPORT hipError_t hipDeviceSynchronize() { return hipSuccess; }  // the other device's
 EXPORT hipError_t hipEventCreate(hipEvent_t*) { return hipSuccess; }
 EXPORT hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
@@ -131,6 +141,15 @@ int main() {
 }
 """
 
+MAIN_YIELD = r"""
+int main() {
+    queries_busy = 1000;  // 2 ms apart
+    CHECK(call((hipStream_t)1, false) == TK_OK);
+    CHECK(yields > 0 && queries_busy == 1000);
+    return 0;
+}
+"""
+
 
 def _run(tmp_path, main):
     cxx = shutil.which("g++")
@@ -147,3 +166,9 @@ def _run(tmp_path, main):
 
 def test_no_publication_outlives_its_call(tmp_path):
     _run(tmp_path, MAIN_PENDING)
+
+
+def test_a_wait_lets_other_threads_run(tmp_path):
+    """The wait for a rank spans a whole Gram: on a machine with fewer cores than
+    threads it has to give its core away between looks."""
+    _run(tmp_path, MAIN_YIELD)
