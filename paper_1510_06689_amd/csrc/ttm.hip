@@ -302,17 +302,33 @@ static int pick_kb(const T* y, const ModeView& v, const double* m, int64_t ldm, 
     return fail(TK_ERR_UNSUPPORTED, "ttm: no tile for K=%d", K);
 }
 
+// Many output rows of a wide mode and a large tensor are product-bound: the
+// operator goes to registers there.  J = 128, K = 64: 0.39 -> 0.33 ms (FP64,
+// 0.8 GB), FP32 0.63 -> 0.31; J = 250, K = 100: 140 -> 94 us.  Up to K = 32 or
+// J = 64 the tensor's bytes take longer and ttm_f64_kernel, which starts faster
+// and keeps more loads under way, is ahead (J = 64, K = 48 FP64: 73 against 86
+// us; J = 128, K = 20, 26 MB: 15 against 18 us).  From J = 65 to 95 the products
+// with the rows past J, up to 128, cost as much as the registers gain (FP64, 8
+// to 200 million elements: 0.85 to 1.27 times ttm_f64_kernel's time).
+//
+// The operator's way into the registers is 5 to 20 us that only many tiles
+// earn back.  In tiles per CU (times groups of output rows), the time against
+// ttm_f64_kernel's over J = 96 .. 256, K = 33 .. 200, L = 1, 20, 100, both types:
+//   up to 1: 0.82 - 2.45   1 to 3: 0.73 - 1.52   above 8: 0.44 - 1.05
+//   3 to 8:  0.79 - 1.07 below J = 112, 0.56 - 1.04 from there to J = 192 and for
+//            K > 64, 0.74 - 1.14 above with K <= 64 (6 to 8: 0.74 - 0.95).
+static bool ttm_takes_reg(const ModeView& v, int64_t K) {
+    if (K <= 32 || v.J < 96 || v.J > 256) return false;
+    const int kt = v.J <= 128 ? kRegKt<128> : kRegKt<256>, rows = K <= 64 ? 64 : 128;
+    const int least = v.J < 112 ? 8 : v.J > 192 && K <= 64 ? 6 : 3;
+    const double tiles = (double)make_tiles(v, kt).ntiles * (double)((K + rows - 1) / rows);
+    return tiles > (double)least * device_cu_count();
+}
+
 template <typename T>
 static int dispatch_ttm(const T* y, const ModeView& v, const double* m, int64_t K, int64_t ldm,
                         int transpose, T* z, hipStream_t st) {
-    // Many output rows of a wide mode are product-bound: the operator goes to
-    // registers there.  J = 128, K = 64: 0.39 -> 0.33 ms (FP64, 0.8 GB), FP32
-    // 0.63 -> 0.31; J = 250, K = 100: 140 -> 94 us.  Up to K = 32 or J = 64 the
-    // tensor's bytes take longer and the kernel below, which starts faster and
-    // keeps more loads under way, is ahead (J = 64, K = 48 FP64: 73 against 86
-    // us; J = 128, K = 20, 26 MB: 15 against 18 us).
-    if (K > 32 && v.J > 64 && v.J <= 256)
-        return launch_ttm_reg(y, v, m, ldm, (int)K, transpose, z, st);
+    if (ttm_takes_reg(v, K)) return launch_ttm_reg(y, v, m, ldm, (int)K, transpose, z, st);
     switch (round_pow2(v.J, 32)) {
         case 32: return pick_kb<T, 32>(y, v, m, ldm, (int)K, transpose, z, st);
         case 64: return pick_kb<T, 64>(y, v, m, ldm, (int)K, transpose, z, st);
