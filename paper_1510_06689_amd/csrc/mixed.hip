@@ -1505,6 +1505,8 @@ static int mt_pick_kb(const float* y, const ModeView& v, const double* m, int64_
     return fail(TK_ERR_UNSUPPORTED, "bf16 ttm: no tile for K=%d", K);
 }
 
+constexpr double kQuadColumns = 128 * 64 * kMtWaves;
+
 template <int NKS, bool X3>
 static int mt_launch_quad(const float* y, const ModeView& v, const double* m, int64_t ldm, int K,
                           int transpose, float* z, hipStream_t st) {
@@ -1532,7 +1534,15 @@ template <bool X3>
 static int mt_dispatch(const float* y, const ModeView& v, const double* m, int64_t ldm, int K,
                        int transpose, float* z, hipStream_t st) {
     const int nks = (v.J + 31) / 32;
-    if (v.L % 4 == 0 && v.L >= 16 && nks <= 4 && (uintptr_t)y % 16 == 0 && (uintptr_t)z % 16 == 0) {
+    // The 64-column kernel needs enough columns for its waves, a quarter of the
+    // other's.  Its time against the other's over J = 1 .. 128, K = 4 .. 300, L = 16
+    // .. 1000: up to 64 workgroups of 256 columns 0.50 to 2.71 (median 1.12, above K
+    // = 128 1.96), from there to 128 0.34 to 1.42 (1.03; 0.95), above 0.15 to 1.17
+    // (0.84; 0.61), 20 of 1940 sizes being slower by more than 5%.  J = 64, K = 64,
+    // L = 100: 7800 columns 8.4 -> 9.4 us, 78100 18.2 -> 15.2, 312500 47.9 -> 39.3.
+    const bool many = (double)v.L * (double)v.B > kQuadColumns;
+    if (many && v.L % 4 == 0 && v.L >= 16 && nks <= 4 && (uintptr_t)y % 16 == 0 &&
+        (uintptr_t)z % 16 == 0) {
         switch (nks) {
             case 1: return mt_launch_quad<1, X3>(y, v, m, ldm, K, transpose, z, st);
             case 2: return mt_launch_quad<2, X3>(y, v, m, ldm, K, transpose, z, st);
