@@ -248,30 +248,54 @@ static GramPlan plan_narrow(const ModeView& v, int elem_bytes) {
     return pl;
 }
 
+// Few columns, whose tiles don't fill the chip, take other schedules; the line
+// is about where they stop to pay.  Times against one tile per workgroup of the
+// schedules for many columns, both types, L = 1 .. 300:
+//   J <= 64: tiles of 32 columns instead of 64 or 128, which a small tensor
+//     doesn't fill.  J = 17 .. 64: 100 columns 0.75 - 0.91, 1500 0.83 - 0.98,
+//     3500 0.85 - 1.04, 4500 0.95 - 1.06, 8000 1.00 - 1.34 (more partials to
+//     reduce).
+//   J > 160: the block pairs over many workgroups (gram_partial_wide), so that a
+//     tile's products are spread, and at most 32 ranges of tiles, since every
+//     range costs the reduction a partial per pair.  J = 161 .. 512: 600 columns
+//     0.65 - 0.89, 3000 0.67 - 0.99, 4000 0.73 - 1.05, 6000 0.82 - 1.20.  (16
+//     ranges took 0.82 - 1.13 times the time of 32 at 600 columns and 1.00 - 1.48
+//     at 3000, 64 ranges 1.04 - 1.30 and 0.92 - 1.15.)  J = 145: 0.82 - 0.89, 0.94
+//     - 1.04, 0.99 - 1.10, not worth a stage of its own.
+constexpr double kFewColumns = 4096;
+constexpr int kFewRanges = 32;
+
 static GramPlan plan_tiled(const ModeView& v) {
     GramPlan pl{};
     pl.nb = (v.J + 15) / 16;
     pl.npairs = pl.nb * (pl.nb + 1) / 2;
+    const bool few = (double)v.L * (double)v.B <= kFewColumns;
     int64_t want = device_cu_count();
+    pl.G = 1;
     if (pl.nb <= 16) {
-        pl.G = 1;
         with_blocks(pl.nb, [&](auto nbc) {
-            typedef GramSched<decltype(nbc)::value> S;
-            pl.KT = S::KT;
-            want *= S::kPerCu;
+            constexpr int NB = decltype(nbc)::value;
+            pl.KT = few && NB <= 4 ? GramSched<NB, true>::KT : GramSched<NB>::KT;
+            want *= GramSched<NB>::kPerCu;
             return (int)TK_OK;
         });
     } else {
         pl.KT = kWideKt;
         pl.G = (pl.npairs + kWidePairs - 1) / kWidePairs;
-        want /= pl.G;
+        want = xcd_round_want(want / pl.G, pl.G);
+    }
+    pl.partial_bound = (size_t)want * pl.npairs * 256 * sizeof(double);
+    if (few && pl.nb > 10) {
+        pl.KT = kWideKt;
+        want = want < kFewRanges ? want : kFewRanges;
+        const int64_t p = xcd_ranges(make_tiles(v, pl.KT).ntiles, want, 2);
+        int G = device_cu_count() / (int)p;
+        if (G > pl.npairs / 16) G = pl.npairs / 16;
+        if (G > pl.G) pl.G = G;
     }
     pl.pairs_per_group = (pl.npairs + pl.G - 1) / pl.G;
-    TileMap tm = make_tiles(v, pl.KT);
-    want = xcd_round_want(want, pl.G);
-    pl.P = xcd_ranges(tm.ntiles, want, pl.G);
+    pl.P = xcd_ranges(make_tiles(v, pl.KT).ntiles, want, pl.G);
     pl.partial_bytes = (size_t)pl.P * pl.npairs * 256 * sizeof(double);
-    pl.partial_bound = (size_t)want * pl.npairs * 256 * sizeof(double);
     return pl;
 }
 

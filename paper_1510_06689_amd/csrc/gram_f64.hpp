@@ -44,13 +44,14 @@ __device__ __forceinline__ void pair_of(int p, int nb, int& bi, int& bj) {
 //   above:   8 waves, each with an eighth of the pairs.
 // Up to NB = 8 a CU has two workgroups, one multiplying while the other stands
 // at its barrier.  KT, the tile's columns: what LDS holds; small extents take
-// wide tiles, which keep more loads in flight.
-template <int NB>
+// wide tiles, which keep more loads in flight (FEW, up to NB = 4: 32 columns,
+// for tensors that fill few tiles).
+template <int NB, bool FEW = false>
 struct GramSched {
     static constexpr int W = NB <= 8 ? 4 : 8;
     static constexpr int T = 64 * W;  // threads
     static constexpr int KS = NB <= 6 ? W : 1;
-    static constexpr int KT = NB <= 2 ? 128 : NB <= 4 ? 64 : 32;
+    static constexpr int KT = NB <= 2 && !FEW ? 128 : NB <= 4 && !FEW ? 64 : 32;
     static constexpr int NP = NB * (NB + 1) / 2;
     static constexpr int NPW = KS == 1 ? (NP + W - 1) / W : NP;
     static constexpr int kLds = 2 * kTileBuf<NB, KT>;  // doubles
@@ -75,11 +76,11 @@ __device__ __forceinline__ int frag_col(int k4) { return 16 * (k4 & 1) + (k4 >> 
 // (81 MB).  SKIP (batches, J
 // below the extent class): pairs with a block at or past ceil(J / 16) sum
 // zeros only and skip their products (their partials stay 0).
-template <typename T, int NB, bool SKIP, bool PACKED>
+template <typename T, int NB, bool FEW, bool SKIP, bool PACKED>
 __device__ __forceinline__ void gram_f64_walk(const T* __restrict__ y, const TileMap& tm,
                                               int64_t t0, int64_t t1, double* __restrict__ out,
                                               double* lds) {
-    typedef GramSched<NB> S;
+    typedef GramSched<NB, FEW> S;
     constexpr int P = S::KT + 1, NPW = S::NPW, NP = S::NP, BUF = kTileBuf<NB, S::KT>;
     constexpr int KQ = S::KT / 8 / S::KS;  // steps of eight columns, of a wave per tile
     constexpr bool ALL = S::KS > 1;        // a wave has all pairs
@@ -219,26 +220,28 @@ __device__ __forceinline__ void gram_f64_walk(const T* __restrict__ y, const Til
     }
 }
 
-template <typename T, int NB, bool SKIP>
+template <typename T, int NB, bool FEW, bool SKIP>
 __device__ __forceinline__ void gram_f64_body(const T* __restrict__ y, const TileMap& tm,
                                               int64_t t0, int64_t t1, double* __restrict__ out,
                                               double* lds) {
-    for (int e = threadIdx.x; e < GramSched<NB>::kLds; e += GramSched<NB>::T) lds[e] = 0.0;
+    typedef GramSched<NB, FEW> S;
+    for (int e = threadIdx.x; e < S::kLds; e += S::T) lds[e] = 0.0;
     if (tm.packed)
-        gram_f64_walk<T, NB, SKIP, true>(y, tm, t0, t1, out, lds);
+        gram_f64_walk<T, NB, FEW, SKIP, true>(y, tm, t0, t1, out, lds);
     else
-        gram_f64_walk<T, NB, SKIP, false>(y, tm, t0, t1, out, lds);
+        gram_f64_walk<T, NB, FEW, SKIP, false>(y, tm, t0, t1, out, lds);
 }
 
 // P tile ranges, one workgroup each; J <= 256.
-template <typename T, int NB>
-__global__ __launch_bounds__(GramSched<NB>::T, 2) void gram_partial_f64(
+template <typename T, int NB, bool FEW>
+__global__ __launch_bounds__((GramSched<NB, FEW>::T), 2) void gram_partial_f64(
     const T* __restrict__ y, TileMap tm, int P, double* __restrict__ partial) {
     extern __shared__ double lds[];
     const int p = blockIdx.x;
     const int64_t t0 = tm.ntiles * (int64_t)p / P;
     const int64_t t1 = tm.ntiles * (int64_t)(p + 1) / P;
-    gram_f64_body<T, NB, false>(y, tm, t0, t1, partial + (int64_t)p * GramSched<NB>::NP * 256, lds);
+    gram_f64_body<T, NB, FEW, false>(y, tm, t0, t1, partial + (int64_t)p * GramSched<NB>::NP * 256,
+                                     lds);
 }
 
 // J > 256: 153 to 528 block pairs do not fit one workgroup's accumulators, so
@@ -246,6 +249,7 @@ __global__ __launch_bounds__(GramSched<NB>::T, 2) void gram_partial_f64(
 // range (P ranges x G groups, one workgroup each, xcd_range_group).  J = 400
 // FP32, 93 MB: 404 -> 210 us, J = 512 FP64, 164 MB: 412 -> 370 us, J = 301
 // FP64 unchanged (139 us), against nine groups and a stage of 512 rows.
+// J > 160 takes it too where there are few columns, in many small groups.
 constexpr int kWideThreads = 512, kWideWaves = kWideThreads / 64;
 constexpr int kWideNpw = 14, kWidePairs = kWideWaves * kWideNpw, kWideKt = 16;
 // NB: the block count rounded up to a multiple of four (it sizes the stage).
@@ -347,17 +351,23 @@ template <typename T>
 static int launch_gram_f64_t(const T* y, const ModeView& v, const GramPlan& pl, double* partial,
                             hipStream_t st) {
     const TileMap tm = make_tiles(v, pl.KT);
-    if (pl.nb <= 16)
+    if (pl.KT != kWideKt)
         return with_blocks(pl.nb, [&](auto nbc) -> int {
             constexpr int NB = decltype(nbc)::value;
-            const size_t lds = GramSched<NB>::kLds * sizeof(double);
-            auto fn = gram_partial_f64<T, NB>;
-            TK_HIP(hipFuncSetAttribute((const void*)fn,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            hipLaunchKernelGGL(fn, dim3(pl.P), dim3(GramSched<NB>::T), lds, st, y, tm, pl.P,
-                               partial);
-            TK_HIP(hipGetLastError());
-            return TK_OK;
+            auto launch = [&](auto few) -> int {
+                constexpr bool FEW = decltype(few)::value;
+                typedef GramSched<NB, FEW> S;
+                const size_t lds = S::kLds * sizeof(double);
+                auto fn = gram_partial_f64<T, NB, FEW>;
+                TK_HIP(hipFuncSetAttribute((const void*)fn,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+                hipLaunchKernelGGL(fn, dim3(pl.P), dim3(S::T), lds, st, y, tm, pl.P, partial);
+                TK_HIP(hipGetLastError());
+                return TK_OK;
+            };
+            if constexpr (NB <= 4)
+                if (pl.KT != GramSched<NB>::KT) return launch(std::true_type{});
+            return launch(std::false_type{});
         });
     if (v.J > TK_MAX_MODE_DIM)
         return fail(TK_ERR_UNSUPPORTED, "mode extent %d exceeds %d", v.J, TK_MAX_MODE_DIM);
@@ -372,6 +382,7 @@ static int launch_gram_f64_t(const T* y, const ModeView& v, const GramPlan& pl, 
         TK_HIP(hipGetLastError());
         return TK_OK;
     };
+    if (pl.nb <= 16) return launch(std::integral_constant<int, 16>{});
     if (pl.nb <= 20) return launch(std::integral_constant<int, 20>{});
     if (pl.nb <= 24) return launch(std::integral_constant<int, 24>{});
     if (pl.nb <= 28) return launch(std::integral_constant<int, 28>{});

@@ -31,8 +31,8 @@ __global__ __launch_bounds__(GramSched<JB / 16>::T, 2) void gram_f64_batched(
     if (w >= active) return;  // uniform over the workgroup
     const int64_t t0 = tm.ntiles * (int64_t)w / active;
     const int64_t t1 = tm.ntiles * (int64_t)(w + 1) / active;
-    gram_f64_body<float, JB / 16, true>(tk.y, tm, t0, t1, tk.partial + (int64_t)w * S::NP * 256,
-                                        lds);
+    gram_f64_body<float, JB / 16, false, true>(tk.y, tm, t0, t1,
+                                               tk.partial + (int64_t)w * S::NP * 256, lds);
 }
 
 template <int JB>
