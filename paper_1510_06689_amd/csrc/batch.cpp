@@ -47,8 +47,8 @@ struct GramLaunch {
 bool f64_class(int jb) { return jb <= 32; }
 
 // Workgroups of one problem's Gram: its tiles over tiles-per-workgroup.  An
-// FP64 class's problems are small and its kernel walks finer tiles, so it
-// takes a quarter of the tiles per workgroup (more workgroups in flight).
+// FP64 class's problems are small, so it takes a quarter of the tiles per
+// workgroup (more workgroups in flight; both kernels' tiles have 128 columns).
 int gram_wgs(int64_t ntiles, int tpw, int jb, int cap) {
     const int t = f64_class(jb) ? std::max(1, tpw / 4) : tpw;
     return std::max(1, std::min(cap, (int)((ntiles + t - 1) / t)));

@@ -131,7 +131,8 @@ size_t eig_scratch_doubles(int J) {
     return J > 128 ? (size_t)3 * J * J + (size_t)6 * J + 64 : (size_t)2 * J * J + 64;
 }
 
-// small per-matrix arrays + the [C][rb] partial sums of the tridiagonal step
+// small per-matrix arrays, and room for the four vector buffers of the register
+// reduction (4 JP <= 512 doubles of the last 1024)
 static size_t eig_small_doubles(int J) { return (size_t)8 * J + 64 + 8 + (size_t)kEigThreads; }
 
 // LDS doubles for the matrix (J <= 128) and later the inverse-iteration
@@ -282,7 +283,8 @@ __device__ __forceinline__ double row16_sum(double v) {
 // diagonal, off-diagonal and reflector scalars go to d, e, beta at offset
 // koff, and reflector koff + k (length Jr - k - 1) to H[(koff + k) J ..].
 // With koff = 0, Jr = J this is the whole reduction; with koff > 0 it
-// finishes one whose first koff steps ran on the matrix in global memory.
+// finishes one whose first koff columns the kernels for extents above 128 have
+// reduced.
 template <int JP>
 __device__ __forceinline__ void tridiag_regs(const double* __restrict__ src, int ld, int Jr,
                                              int koff, int J, double* reg, double* red,
@@ -315,11 +317,10 @@ __device__ __forceinline__ void tridiag_regs(const double* __restrict__ src, int
     double* Hs = reg;
     // Every load below stays inside the reflector store (zeroed first, so
     // that entries no step writes are exact zeros: reflector k is written
-    // from column k + 1 on) and four JP-long vector buffers in the
-    // 1024-double area after misc (zeroed too; the global-A path alone uses
-    // it otherwise).  Finished rows and columns see v = p = 0, so the
+    // from column k + 1 on) and four JP-long vector buffers in the area after
+    // misc (zeroed too).  Finished rows and columns see v = p = 0, so the
     // register loops need no masks.
-    static_assert(4 * JP <= kEigThreads, "vector buffers must fit the partial-sum area");
+    static_assert(4 * JP <= kEigThreads, "vector buffers must fit the area after misc");
     double* vbuf = red + 64 + 8;
     for (int i = tid; i < 4 * JP; i += kEigThreads) vbuf[i] = 0.0;
     for (int i = tid; i < (Jr > 2 ? Jr - 2 : 0) * JP; i += kEigThreads) Hs[i] = 0.0;
@@ -1075,13 +1076,12 @@ __device__ __forceinline__ void signed_store(double* __restrict__ X, int J, int 
                 }
 }
 
-// JP = 32, 64, 128: A lives in registers during the tridiagonalisation
-// (J <= JP); JP = 0: A lives in the global scratch (J > 128).
+// JP = 32, 64, 96, 128: A lives in registers during the tridiagonalisation
+// (J <= JP); JP = 0: J > 128, PH = 3 only (launch_eig_reduce does the rest).
 // PH = 0: the whole solver in one launch.  PH = 1: steps 1 and the scaling of
-// T, then T, beta and the bounds go to the hand-off area (the first 6 J + 4
-// doubles of the scratch, A's area, unused or free by then) and the launch
-// ends; eig_multisect then finds the eigenvalues with one workgroup each and
-// PH = 3 picks everything up for steps 3 to 5.
+// T, then T, beta and the bounds go to the hand-off area (eig_handoff) and the
+// launch ends; eig_multisect then finds the eigenvalues with one workgroup each
+// and PH = 3 picks everything up for steps 3 to 5.
 // MULTI (PH = 3): one workgroup per batch of vectors.  Each repeats the rank
 // rule (the first one writes its results) and runs the inverse iteration of
 // its own batch.  With J <= 128 and a rank of one batch the first workgroup
@@ -1289,7 +1289,10 @@ __device__ __forceinline__ void eig_body(const EigArgs& a, int region) {
     // this is the chain from row to row of one wave, about 400 cycles in the
     // factorisation and 230 per iteration; each thread walks half the rows
     // (the launch at J = 128, 16 vectors 114 -> 92 us, J = 100 66 -> 53,
-    // J = 250, 100 vectors 102 -> 64).
+    // J = 250, 100 vectors 102 -> 64).  Two sets of four rows beside the rest of
+    // the kernel exceed the 128 registers of a 1024-thread workgroup: PH = 3
+    // with J <= 128 keeps 68 bytes per lane in scratch memory, PH = 0 spills 5
+    // registers (24 bytes); JP = 0 and the batched kernels have no scratch.
     // Each thread works on a record of its own in
     // LDS: row i holds (x, reciprocal pivot, u1, u2, multiplier, pivot flag)
     // at rec[kLuArrays i ..], so every access is the thread's base plus an
@@ -2022,8 +2025,8 @@ static size_t eig_region_doubles_jp(int J, int JP) {
     return r < hs ? hs : r;
 }
 
-// Register layouts: 32, 64, 96 and 128 rows (8 lanes per row, 8 columns
-// per register block); larger extents take the global-memory path (0).
+// Register layouts: 32, 64, 96 and 128 rows (16 lanes per two rows, columns in
+// blocks of 16); larger extents (0) are brought to 128 rows first.
 static int eig_jp(int J) { return J <= 32 ? 32 : J <= 64 ? 64 : J <= 96 ? 96 : J <= 128 ? 128 : 0; }
 
 size_t eig_lds_bytes(int J) {
@@ -2125,7 +2128,8 @@ int launch_eig_reduce(const double* s, int J, double* scratch, int* flags, int p
 template <int JP>
 static int launch_eig_jp(const EigArgs& a, int region, size_t lds, hipStream_t st) {
     if constexpr (JP > 0) {
-        if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, 1, st);
+        if constexpr (JP <= kSplitEig)  // the extents of 96 and 128 rows all split
+            if (a.J < kSplitEig) return launch_eig_phase<JP, 0>(a, region, lds, 1, st);
         TK_TRY((launch_eig_phase<JP, 1>(a, region, lds, 1, st)));
     } else {
         TK_TRY(launch_eig_reduce(a.s, a.J, a.scratch, a.flags, kGridPolls, st));
@@ -2145,7 +2149,7 @@ int launch_eig(const EigArgs& a, hipStream_t st) {
     const int region = (int)eig_region_doubles_jp(a.J, JP);
     const size_t lds = ((size_t)region + eig_small_doubles(a.J)) * sizeof(double);
     switch (JP) {
-        case 32: return launch_eig_jp<32>(a, region, lds, st);
+        case 32: return launch_eig_phase<32, 0>(a, region, lds, 1, st);  // below kSplitEig
         case 64: return launch_eig_jp<64>(a, region, lds, st);
         case 96: return launch_eig_jp<96>(a, region, lds, st);
         case 128: return launch_eig_jp<128>(a, region, lds, st);

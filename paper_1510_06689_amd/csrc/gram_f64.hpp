@@ -64,18 +64,21 @@ __device__ __forceinline__ int frag_col(int k4) { return 16 * (k4 & 1) + (k4 >> 
 // One workgroup's share, tiles [t0, t1): writes NP * 256 partial sums at
 // `out`, in pair_of order.  While the products of tile t run, the stage's
 // elements of tile t + 1 go to the other buffer and those of tile t + 2 are
-// loaded, a few after each k-step.  Bound by FP64 MFMA issue from J = 64 or so
-// up (64 cycles a product per SIMD), below that by HBM; at J = 128 on 8.6 GB
-// the clock falls to 1.9 GHz and the matrix cores are busy 77% of it (49
-// TFLOP/s of products done, 44 counted; a loop of products alone reaches 77 at
-// 2.4 GHz), and schedules with fewer LDS reads or other workgroup shapes came
-// within 5%.  Before and after (one conversion per load, a branch per element,
-// all pairs rounded up to 32, 64, 128, 256 rows): J = 128 FP64 3.46 -> 3.16 ms
-// (8.6 GB), FP32 0.61 -> 0.30 ms (0.4 GB); J = 250, L = 10 1.23 -> 0.94 ms
-// (1.25 GB); J = 25 1.04 -> 0.67 ms (3.1 GB, 4.6 TB/s); J = 97 57 -> 40 us
-// (81 MB).  SKIP (batches, J
-// below the extent class): pairs with a block at or past ceil(J / 16) sum
-// zeros only and skip their products (their partials stay 0).
+// loaded, a few after each k-step.  Below J = 64 or so HBM bounds it; above,
+// the products and what feeds them: at J = 128 on 8.6 GB it does 49 TFLOP/s of
+// products (44 counted), where an FP64 GEMM of the library reaches 70 on this
+// card, so this is not the card's limit.  A wave takes consecutive pairs of the
+// list and reads both fragments of each from LDS, 18 reads per nine products; 26
+// reads per 36 products (a set of pairs per wave at compile time) were 5% faster
+// there and took sixteen minutes to build.  Before and after (one conversion per
+// load, a branch per element, all pairs rounded up to 32, 64, 128, 256 rows): J =
+// 128 FP64 3.46 -> 3.16 ms (8.6 GB), FP32 0.61 -> 0.30 ms (0.4 GB); J = 250, L =
+// 10 1.23 -> 0.94 ms (1.25 GB); J = 25 1.04 -> 0.67 ms (3.1 GB, 4.6 TB/s); J = 97
+// 57 -> 40 us (81 MB).  From NB = 13 on 12 to 17 accumulators and 16 staged
+// doubles per lane exceed 256 registers: 17, 6, 11 and 31 are spilled (FP32 0,
+// 28, 12, 16).
+// SKIP (batches, J below the extent class): pairs with a block at or past
+// ceil(J / 16) sum zeros only and skip their products (their partials stay 0).
 template <typename T, int NB, bool FEW, bool SKIP, bool PACKED>
 __device__ __forceinline__ void gram_f64_walk(const T* __restrict__ y, const TileMap& tm,
                                               int64_t t0, int64_t t1, double* __restrict__ out,
