@@ -95,12 +95,15 @@ static int check(int jmax) {
 template <int NB>
 static int gram() {
     constexpr int KT = NB <= 2 ? 128 : NB <= 4 ? 64 : 32, THREADS = NB <= 8 ? 256 : 512;
+    if constexpr (NB <= 4)
+        if (check<double, NB, 32, THREADS>(16 * NB)) return 1;
     return check<double, NB, KT, THREADS>(16 * NB) || check<float, NB, KT, THREADS>(16 * NB);
 }
 
 int main() {
     return gram<1>() || gram<2>() || gram<3>() || gram<4>() || gram<5>() || gram<6>() || gram<7>() || gram<8>() ||
-           gram<9>() || gram<12>() || gram<13>() || gram<16>() || check<double, 20, 16, 512>(320) ||
+           gram<9>() || gram<12>() || gram<13>() || gram<16>() || check<float, 16, 16, 512>(256) ||
+           check<double, 20, 16, 512>(320) ||
            check<float, 24, 16, 512>(384) || check<double, 28, 16, 512>(448) || check<float, 32, 16, 512>(512) ||
            check<double, 8, 64, 512>(128) || check<float, 12, 32, 512>(192) || check<double, 16, 32, 512>(256);
 }
